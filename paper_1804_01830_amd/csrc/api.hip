@@ -118,7 +118,7 @@ Shape make_shape(const ddstress_desc* d) {
     // A strip block carries one realisation with one cache line per value;
     // with few realisations it would outlast the other blocks of the launch.
     s.zstrip = s.B >= kZStripBatch;
-    s.tkz = default_z_tk(s.P[2], s.C, s.zg, s.elem);
+    s.tkz = default_z_tk(s.P[2], s.C, s.zg, s.B, s.elem);
     s.ntz = (s.M1 + s.tkz - 1) / s.tkz;
     set_mirrors(s, predict_mirror(d, 1), predict_mirror(d, 2));
     s.sgn_y = s.sgn_z = 0;

@@ -159,6 +159,7 @@ struct ZGeom {
     int64_t ors, oqs, oos; // output strides (6B planes)
     int strip;             // the spectrum keeps the Nyquist strip where the tiles allow it
     int nyq;               // groups of the Nyquist strip (z_nyq_groups; set by launch_z_fused)
+    int sb;                // realisations per block of the strip (set by launch_z_fused)
 };
 // Plans of at least this many realisations keep the Nyquist strip.
 constexpr int kZStripBatch = 4;
@@ -195,7 +196,7 @@ bool ev_col_ok(int ev);
 bool ev_z_ok(int N, int ev, int elem_bytes);
 int default_col_tk(int N, int elem_bytes);
 int default_rows(int M, int elem_bytes);
-int default_z_tk(int N, int C, int groups, int elem_bytes);
+int default_z_tk(int N, int C, int groups, int B, int elem_bytes);
 size_t z_lds_bytes(int N, int tk, int C, int groups, int elem_bytes);
 int z_lds_ld(int tk, int elem_bytes);
 bool z_groups_ok(int groups, int C);
@@ -208,6 +209,16 @@ bool z_stage_spec(int N, int tk, int C, int nkz, int B, int elem_bytes);
 constexpr int kZWaveTile = 8;
 bool z_wave_form(int N, int ev, int groups, int elem_bytes);
 size_t z_wave_lds_bytes(int N, int C, int nkz, int B);
+
+// The register form of the fused z pass (zreg.hpp, z_reg_f32.hip): FP32, one
+// thread group, element class 4, its own tile width, where several
+// realisations share a tile. Same bits as the other forms.
+bool z_reg_applies(int N, int C, int B);
+int z_reg_tile(int N);
+int z_reg_waves(int B);                  // waves per block
+size_t z_reg_lds_bytes(int N, int C, int nkz);
+void z_reg_dispatch(int N, int C, const cplx<float>* in, cplx<float>* out, const float* spec, const ZGeom& g,
+                    const cplx<float>* tw, int64_t blocks, hipStream_t s);
 
 // Fused z launch for C = NC channels and one form (zfused.hpp; instantiated
 // per form and precision in z_serial_f32.hip, z_grouped_f64.hip, ...).

@@ -208,9 +208,9 @@ int z_max_threads(int groups) { return groups == 1 ? 512 : 768; }
 bool z_groups_ok(int groups, int C) { return groups == 1 || groups == C; }
 // Many realisations amortise the grouped form's larger blocks; it is the
 // default from 16 realisations on, where one column per group fits a block
-// (threads and LDS).
+// (threads and LDS) and the register form does not apply.
 int default_z_groups(int N, int C, int B, int elem_bytes) {
-    if (B < 16) return 1;
+    if (B < 16 || (elem_bytes == 4 && z_reg_applies(N, C, B))) return 1;
     const int ev = default_ev_z(N, C, elem_bytes);
     const int e = N < ev ? N : ev;
     const bool fits = z_threads(N, C, 1, e) <= z_max_threads(C) && z_lds_bytes(N, 1, C, C, elem_bytes) <= 64 * 1024;
@@ -295,7 +295,8 @@ int default_rows(int M, int elem_bytes) {
     return rows;
 }
 
-int default_z_tk(int N, int C, int groups, int elem_bytes) {
+int default_z_tk(int N, int C, int groups, int B, int elem_bytes) {
+    if (elem_bytes == 4 && groups == 1 && z_reg_applies(N, C, B)) return z_reg_tile(N);
     const int tc = N / ecount(N, default_ev_z(N, groups, elem_bytes));
     int tk;
     if (groups == 1) {
@@ -511,7 +512,10 @@ void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, 
     ZGeom g = geom;
     g.nyq = g.strip ? z_nyq_groups(g.ncols, tk, g.nky) : 0;
     // tiles x ky rows; in place of the Nyquist strip's tile, its groups x realisations
-    const int64_t blocks = g.nyq > 0 ? (int64_t)(g.ntiles - 1) * g.nky + (int64_t)g.nyq * g.B
+    // the register form takes over wherever its tile and enough realisations are given
+    const bool reg = sizeof(T) == 4 && groups == 1 && ev == 4 && z_reg_applies(N, g.C, g.B) && tk == z_reg_tile(N);
+    g.sb = reg ? z_reg_waves(g.B) : 1;
+    const int64_t blocks = g.nyq > 0 ? (int64_t)(g.ntiles - 1) * g.nky + (int64_t)g.nyq * ((g.B + g.sb - 1) / g.sb)
                                      : (int64_t)g.ntiles * g.nky;
     if (blocks <= 0) return;
     if (blocks > 0x7fffffffLL) fail(DDSTRESS_E_UNSUPPORTED, "grid too large for one launch");
@@ -524,6 +528,13 @@ void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, 
     } else if (tk < 1 || z_threads(N, groups, tk, ev) > z_max_threads(groups) ||
                z_lds_bytes(N, tk, g.C, groups, (int)sizeof(T)) > 64 * 1024) {
         fail(DDSTRESS_E_INVALID, "fused z block exceeds the thread or LDS limit");
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (reg) {
+            z_reg_dispatch(N, g.C, in, out, spec, g, tw, blocks, s);
+            check_hip(hipGetLastError(), "fused z launch");
+            return;
+        }
     }
     // one instance per channel count: the channel loops are unrolled
     const bool grouped = groups != 1;

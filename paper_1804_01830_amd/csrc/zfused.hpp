@@ -62,8 +62,9 @@ __device__ __forceinline__ NyquistRole nyquist_role(int tile, int tk, int col, i
 // workgroups, which the hardware deals to the eight XCDs in turn (so each
 // XCD gets its share of them); the others go through xcd_block, which gives
 // every XCD a contiguous range of the remaining tiles.
-__device__ __forceinline__ int z_logical_block(const ZGeom& g) {
-    const int b = (int)blockIdx.x, strip = g.nyq * g.B;
+// split: blocks per (tile, ky) and per strip block (neighbours in this order).
+__device__ __forceinline__ int z_logical_block(const ZGeom& g, int split = 1) {
+    const int b = (int)blockIdx.x, strip = g.nyq * ((g.B + g.sb - 1) / g.sb) * split;
     return b < strip ? b : strip + xcd_block(b - strip, (int)gridDim.x - strip);
 }
 struct ZRoles {
@@ -83,11 +84,12 @@ template <typename T>
 __device__ __forceinline__ ZRoles z_roles(int blk, int tk, int c, const ZGeom& g) {
     ZRoles r;
     const int tiles = g.nyq > 0 ? g.ntiles - 1 : g.ntiles;
-    const int strip_blocks = g.nyq * g.B;
+    const int per_group = (g.B + g.sb - 1) / g.sb;
+    const int strip_blocks = g.nyq * per_group;
     if (blk < strip_blocks) {                    // the Nyquist strip
-        const int q = blk / g.B, m = g.ncols - 1;
-        r.b0 = blk - q * g.B;
-        r.b1 = r.b0 + 1;
+        const int q = blk / per_group, m = g.ncols - 1;
+        r.b0 = (blk - q * per_group) * g.sb;
+        r.b1 = min(r.b0 + g.sb, g.B);
         const int ky = q * tk + c;
         const bool valid = 2 * ky <= g.nky;
         const int kyv = valid ? ky : q * tk;
