@@ -12,6 +12,7 @@
 // interaction coefficients when a plan is built.
 #include "ddstress_internal.hpp"
 
+#include <algorithm>
 #include <functional>
 #include <map>
 #include <mutex>
@@ -234,13 +235,14 @@ size_t z_lds_bytes(int N, int tk, int C, int groups, int elem_bytes) {
 // The single-group form stages its spectrum tile (nkz rows of (6C + 1) tk
 // values) in LDS for the compile-time widths tk = 4, 8, 16, when there are
 // realisations to reuse it (B >= 2) and the tile and the exchange block fit
-// 64 KiB together (z lengths up to 256; in FP64 with three channels only,
-// more would spill registers).
+// 64 KiB together (z lengths up to 256), with three channels: with more it
+// was slower than reading the spectrum per realisation (128 x 128 x 16, two
+// realisations, six channels 83 against 58 us, nine 214 against 102).
 size_t z_stage_bytes(int tk, int C, int nkz, int elem_bytes) {
     return (size_t)nkz * (6 * C + 1) * tk * elem_bytes;
 }
 bool z_stage_spec(int N, int tk, int C, int nkz, int B, int elem_bytes) {
-    return B >= 2 && N <= 256 && (tk == 4 || tk == 8 || tk == 16) && (elem_bytes <= 4 || C == 3) &&
+    return B >= 2 && N <= 256 && (tk == 4 || tk == 8 || tk == 16) && C == 3 &&
            z_lds_bytes(N, tk, C, 1, elem_bytes) + z_stage_bytes(tk, C, nkz, elem_bytes) <= 64 * 1024;
 }
 int default_ev_col(int N) { return N <= 64 ? 8 : 16; }
@@ -299,12 +301,22 @@ int default_z_tk(int N, int C, int groups, int B, int elem_bytes) {
     if (elem_bytes == 4 && groups == 1 && z_reg_applies(N, C, B)) return z_reg_tile(N);
     const int tc = N / ecount(N, default_ev_z(N, groups, elem_bytes));
     int tk;
-    if (groups == 1) {
-        const int tk_min = elem_bytes <= 4 ? 16 : 8;
-        tk = 256 / tc;
-        if (tk < tk_min) tk = tk_min;
-    } else {
+    if (groups != 1) {
         tk = 128 / tc;
+    } else if (N > 256) {
+        tk = std::max(elem_bytes <= 4 ? 16 : 8, 256 / tc);
+    } else if (elem_bytes == 4 && N == 64 && C == 3 && B >= 6) {
+        tk = 16;
+    } else {
+        // The smallest blocks that still fill the launch: one wave up to length
+        // 32, two up to 128, four at 256. More of them run at once and each waits
+        // for fewer columns at its barriers; narrower tiles fetch partial cache
+        // lines. Measured (us, this tile / 256 to 512 threads), one realisation:
+        // FP32 128x128 with 4, 8, 16, 32, 64 layers, six channels 10 / 11, 19 / 22,
+        // 31 / 37, 59 / 80, 135 / 185; 256x256x64 510 / 680 and, periodic with nine
+        // channels, 165 / 235; FP64 128x128 with 8, 16, 32 layers, three channels
+        // 18 / 20, 38 / 50, 88 / 98, 64^3 57 / 85.
+        tk = (N <= 32 ? 64 : N <= 128 ? 128 : 256) / tc;
     }
     if (tk < 1) tk = 1;
     while (tk > 1 && (z_lds_bytes(N, tk, C, groups, elem_bytes) > 64 * 1024 ||

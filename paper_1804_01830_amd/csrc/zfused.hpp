@@ -716,7 +716,7 @@ static void z_launch(int64_t blocks, int tk, const cplx<T>* in, cplx<T>* out, co
         }
         hipLaunchKernelGGL((k_z_grouped<T, L, E, NC, false>), dim3((unsigned)blocks), block, lds, s, in, out, spec, g,
                            tw, tk, ld);
-    } else if constexpr (L >= 2 && L <= 256) {
+    } else if constexpr (NC == 3 && L >= 2 && L <= 256) {
         if (z_stage_spec(L, tk, NC, g.nkz_s, g.B, (int)sizeof(T))) {
             lds += z_stage_bytes(tk, NC, g.nkz_s, (int)sizeof(T));
             const dim3 grid((unsigned)blocks);
