@@ -161,8 +161,9 @@ typedef struct {
     int32_t ex, ey, ez;    /* element classes of the x, y and fused z passes (0: default) */
     int32_t z_groups;      /* fused z thread groups: 1 or C (0: default, C when batch >= 16) */
     int32_t yx;            /* inverse y and x: 1 two passes, 2 one fused kernel that keeps each
-                              (realisation, component, z) plane in LDS (FP32 with Py = 256 and
-                              Px = 256 only), 0 default (fused where it applies) */
+                              (realisation, component, z) plane in LDS (by name for FP32 with Py = 256,
+                              Px = 256 and an open y axis only), 0 default (fused wherever a plane
+                              fits: 16 <= Py <= 128 and 16 <= Px <= 256, or the FP32 planes above) */
     int32_t xy;            /* forward x and y: 1 two passes, 2 one fused kernel (same shapes), 0 default */
     float   ms[3];         /* autotune: median device ms of the chosen x pair, y pair and z pass */
 } ddstress_tuning;

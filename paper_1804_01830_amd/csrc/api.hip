@@ -459,14 +459,11 @@ void enqueue_pass(ddstress_plan_s* p, int k, const T* rho, T* sigma, int nb, hip
     const int64_t BC = (int64_t)s.B * s.C;
     const int64_t B6 = (int64_t)s.B * 6;
     const int Nx = s.N[0], Ny = s.N[1], Nz = s.N[2], Py = s.P[1];
-    const bool xy = sizeof(T) == 4 && p->xy;
-    const bool yx = sizeof(T) == 4 && p->yx;
+    const bool xy = p->xy, yx = p->yx;
     if (k == 0) {
-        if constexpr (sizeof(T) == 4) {
-            if (xy) {
-                launch_xy_fwd(rho, w2, BC * Nz, Py, s.M, Ny, Nx, s.wx, tw, st, Nz);   // ky-major
-                return;
-            }
+        if (xy) {
+            launch_xy_fwd<T>(Py, s.M, rho, w2, BC * Nz, Ny, Nx, s.wx, tw, st, Nz);   // ky-major
+            return;
         }
         // x forward: rows (b, c, z, y) of Nx reals -> M+1 complex
         launch_x_r2c<T>(s.M, p->ex, rho, w1, BC * Nz * Ny, Nx, Nx, s.wx, tw, p->rows_x, st);
@@ -484,12 +481,10 @@ void enqueue_pass(ddstress_plan_s* p, int k, const T* rho, T* sigma, int nb, hip
         double* stats_out = stt.stats;
         const double inv_plane = 1.0 / ((double)Nx * (double)Ny);
         if (k == 3) {
-            if constexpr (sizeof(T) == 4) {
-                if (yx) {
-                    launch_yx_inv(w1, sigma, B6 * Nz, Py, s.M, Ny, Nx, s.wx, tw, st, rowsq, Nz);   // ky-major
-                    if (rowsq) launch_rowsq_finish(rowsq, B6 * Nz, Ny, inv_plane, stats_out, st);
-                    return;
-                }
+            if (yx) {
+                launch_yx_inv<T>(Py, s.M, w1, sigma, B6 * Nz, Ny, Nx, s.wx, tw, st, rowsq, Nz);   // ky-major
+                if (rowsq) launch_rowsq_finish(rowsq, B6 * Nz, Ny, inv_plane, stats_out, st);
+                return;
             }
             // y inverse: Py rows -> Ny rows
             launch_col_fft<T>(Py, p->ey, false, w1, w2, inv_y_geom(s, B6), tw, p->tk_y, st);
@@ -508,7 +503,6 @@ StatsTarget plan_stats(const ddstress_plan_s* p) {
 
 // Whether pass k runs inside the previous pass's kernel (and enqueues nothing).
 bool pass_fused_away(const ddstress_plan_s* p, int k) {
-    if (p->shape.elem != 4) return false;
     return (k == 1 && p->xy) || (k == 4 && p->yx);
 }
 
@@ -619,7 +613,12 @@ struct LaunchChoice {
     bool yx, xy;
 };
 
-bool yx_ok(const Shape& s) { return yx_inv_fits(s.P[1], s.M, s.N[1], s.elem); }
+// The default fuses x and y wherever a plane fits; a tuning may ask for it by
+// name for the FP32 planes of Py = 256, Px = 256 with an open y axis.
+bool yx_ok(const Shape& s) { return plane_fits(s.P[1], s.M, s.N[1], s.elem); }
+bool yx_request_ok(const Shape& s) {
+    return yx_ok(s) && s.elem == 4 && s.P[1] == 256 && s.M == 128 && s.N[1] <= s.P[1] / 2;
+}
 
 LaunchChoice default_launch(const Shape& s) {
     return {default_rows(s.M, s.elem), default_ev_col(s.M), default_col_tk(s.P[1], s.elem), default_ev_col(s.P[1]),
@@ -635,7 +634,8 @@ LaunchChoice apply_tuning(Shape& s, const ddstress_tuning* t) {
     const int ez = t->ez ? t->ez : default_ev_z(s.P[2], zg, s.elem);
     if (!rows_ok(s, t->rows_x, ex) || !col_ok(s, s.P[1], t->tk_y, ey) || !z_ok(s, t->tk_z, ez, zg))
         fail(DDSTRESS_E_INVALID, "tuning choice outside the launch limits of this shape");
-    if (t->yx < 0 || t->yx > 2 || (t->yx == 2 && !yx_ok(s)) || t->xy < 0 || t->xy > 2 || (t->xy == 2 && !yx_ok(s)))
+    if (t->yx < 0 || t->yx > 2 || (t->yx == 2 && !yx_request_ok(s)) || t->xy < 0 || t->xy > 2 ||
+        (t->xy == 2 && !yx_request_ok(s)))
         fail(DDSTRESS_E_INVALID, "fused x-y passes do not apply to this shape");
     c = {t->rows_x, ex, t->tk_y, ey, ez, zg, t->yx == 0 ? yx_ok(s) : t->yx == 2, t->xy == 0 ? yx_ok(s) : t->xy == 2};
     s.zg = zg;
@@ -780,7 +780,7 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
     for (auto& z : zlist) {
         const int tk = z.tk, ev = z.ev, groups = z.groups;
         // the layouts of fused x-y passes where they apply (they are chosen below)
-        ZGeom gz = z_geom(s, tk, s.B, sizeof(T) == 4 && yx_ok(s), sizeof(T) == 4 && yx_ok(s));
+        ZGeom gz = z_geom(s, tk, s.B, yx_ok(s), yx_ok(s));
         gz.sgn_y = gz.sgn_z = 0;                 // (the tuning spectrum is zeros)
         float ms = time_median(st, reps, [&] {
             launch_z_fused<T>(Pz, ev, groups, w2.as<cplx<T>>(), w1.as<cplx<T>>(), spec.as<T>(), gz, twp, tk, st);
@@ -797,8 +797,9 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
     // inverse y and x, forward x and y: the chosen separate passes against the fused kernels
     out->yx = 1;
     out->xy = 1;
-    if constexpr (sizeof(T) == 4) {
-        if (yx_ok(s)) {
+    if (yx_ok(s)) {
+        {
+            const int fuse = yx_request_ok(s) ? 2 : 0;       // by name, or as the default
             const ColGeom gi = inv_y_geom(s, B6);
             const float sep = time_median(st, reps, [&] {
                 launch_col_fft<T>(Py, out->ey, false, w1.as<cplx<T>>(), w2.as<cplx<T>>(), gi, twp, out->tk_y, st);
@@ -806,11 +807,10 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
                                 out->rows_x, st);
             });
             const float fused = time_median(st, reps, [&] {
-                launch_yx_inv(w1.as<cplx<float>>(), sig.as<float>(), B6 * Nz, Py, s.M, Ny, Nx, s.wx, twp, st,
-                              nullptr, Nz);
+                launch_yx_inv<T>(Py, s.M, w1.as<cplx<T>>(), sig.as<T>(), B6 * Nz, Ny, Nx, s.wx, twp, st, nullptr, Nz);
             });
             if (verbose) std::fprintf(stderr, "[tune] inverse y+x separate %.5f ms fused %.5f ms\n", sep, fused);
-            if (fused < sep) out->yx = 2;
+            if (fused < sep) out->yx = fuse;
             const ColGeom gy = fwd_y_geom(s, BC);
             const float sepf = time_median(st, reps, [&] {
                 launch_x_r2c<T>(s.M, out->ex, rho.as<T>(), w1.as<cplx<T>>(), BC * Nz * Ny, Nx, Nx, s.wx, twp,
@@ -818,10 +818,10 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
                 launch_col_fft<T>(Py, out->ey, true, w1.as<cplx<T>>(), w2.as<cplx<T>>(), gy, twp, out->tk_y, st);
             });
             const float fusedf = time_median(st, reps, [&] {
-                launch_xy_fwd(rho.as<float>(), w2.as<cplx<float>>(), BC * Nz, Py, s.M, Ny, Nx, s.wx, twp, st, Nz);
+                launch_xy_fwd<T>(Py, s.M, rho.as<T>(), w2.as<cplx<T>>(), BC * Nz, Ny, Nx, s.wx, twp, st, Nz);
             });
             if (verbose) std::fprintf(stderr, "[tune] forward x+y separate %.5f ms fused %.5f ms\n", sepf, fusedf);
-            out->xy = fusedf < sepf ? 2 : 1;
+            out->xy = fusedf < sepf ? fuse : 1;
         }
     }
     check_hip(hipStreamSynchronize(st), "tuning");

@@ -226,16 +226,33 @@ template <typename T, int NC, bool GROUPED>
 void z_dispatch(int N, int ev, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& g,
                 const cplx<T>* tw, int tk, int64_t blocks, hipStream_t s);
 
-// Fused forward x and y, and fused inverse y and x, for planes that fit one
-// block's LDS (yx_fused.hip): FP32, Py = 256, M = 128. The spectrum planes
-// (Py rows of wx complex values) are interleaved in groups of zp: plane p
-// starts at (p / zp) zp Py wx + (p % zp) wx and its rows are zp wx apart
-// (zp = 1: each plane contiguous).
-bool yx_inv_fits(int Py, int M, int ny, int elem_bytes);
-void launch_yx_inv(const cplx<float>* in, float* out, int64_t nplanes, int Py, int M, int ny, int nx, int64_t wx,
-                   const cplx<float>* tw, hipStream_t s, double* rowsq = nullptr, int zp = 1);
-void launch_xy_fwd(const float* in, cplx<float>* out, int64_t nplanes, int Py, int M, int ny, int nx, int64_t wx,
-                   const cplx<float>* tw, hipStream_t s, int zp = 1);
+// Fused forward x and y, and fused inverse y and x, for planes that fit in
+// LDS (plane.hpp). The spectrum planes (Py rows of wx complex values) are
+// interleaved in groups of zp: plane p starts at (p / zp) zp Py wx + (p % zp) wx
+// and its rows are zp wx apart (zp = 1: each plane contiguous).
+bool plane_fits(int Py, int M, int ny, int elem_bytes);
+inline void check_plane_launch(int64_t nplanes, int zp) {
+    if (nplanes > 0x7fffffffLL) fail(DDSTRESS_E_UNSUPPORTED, "grid too large for one launch");
+    if (zp < 1 || nplanes % zp != 0) fail(DDSTRESS_E_INVALID, "plane interleave must divide the plane count");
+}
+template <typename T>
+void launch_yx_inv(int Py, int M, const cplx<T>* in, T* out, int64_t nplanes, int ny, int nx, int64_t wx,
+                   const cplx<T>* tw, hipStream_t s, double* rowsq, int zp);
+template <typename T>
+void launch_xy_fwd(int Py, int M, const T* in, cplx<T>* out, int64_t nplanes, int ny, int nx, int64_t wx,
+                   const cplx<T>* tw, hipStream_t s, int zp);
+template <>
+void launch_yx_inv<float>(int, int, const cplx<float>*, float*, int64_t, int, int, int64_t, const cplx<float>*,
+                          hipStream_t, double*, int);
+template <>
+void launch_yx_inv<double>(int, int, const cplx<double>*, double*, int64_t, int, int, int64_t, const cplx<double>*,
+                           hipStream_t, double*, int);
+template <>
+void launch_xy_fwd<float>(int, int, const float*, cplx<float>*, int64_t, int, int, int64_t, const cplx<float>*,
+                          hipStream_t, int);
+template <>
+void launch_xy_fwd<double>(int, int, const double*, cplx<double>*, int64_t, int, int, int64_t, const cplx<double>*,
+                           hipStream_t, int);
 
 // Every power-of-two transform length the passes support.
 #define DDS_FOR_LENGTHS(X, EV) X(1, EV) X(2, EV) X(4, EV) X(8, EV) X(16, EV) X(32, EV) X(64, EV) \

@@ -70,7 +70,15 @@ __device__ __forceinline__ void dft4(cplx<T>* v) {
     v[3] = csub(t1, t3);
 }
 
-template <bool FWD, typename T>
+// Rounds a product where it stands, so that no addition takes it into an FMA.
+template <typename T>
+__device__ __forceinline__ void round_here(cplx<T>& a) {
+    asm("" : "+v"(a.x), "+v"(a.y));
+}
+
+// APART: the products with the eighth roots are rounded before they are added
+// (otherwise -ffp-contract joins the two).
+template <bool FWD, bool APART = false, typename T>
 __device__ __forceinline__ void dft8(cplx<T>* v) {
     // even/odd split: two length-4 transforms joined with the eighth roots
     cplx<T> e[4] = {v[0], v[2], v[4], v[6]};
@@ -87,6 +95,10 @@ __device__ __forceinline__ void dft8(cplx<T>* v) {
         o1 = {(o[1].x - o[1].y) * h, (o[1].x + o[1].y) * h};
         o3 = {-(o[3].x + o[3].y) * h, (o[3].x - o[3].y) * h};
     }
+    if constexpr (APART) {
+        round_here(o1);
+        round_here(o3);
+    }
     cplx<T> o2 = rot90<FWD>(o[2]);
     v[0] = cadd(e[0], o[0]);
     v[4] = csub(e[0], o[0]);
@@ -98,11 +110,11 @@ __device__ __forceinline__ void dft8(cplx<T>* v) {
     v[7] = csub(e[3], o3);
 }
 
-template <int R, bool FWD, typename T>
+template <int R, bool FWD, bool APART = false, typename T>
 __device__ __forceinline__ void dftR(cplx<T>* v) {
     if constexpr (R == 2) dft2<FWD>(v);
     else if constexpr (R == 4) dft4<FWD>(v);
-    else if constexpr (R == 8) dft8<FWD>(v);
+    else if constexpr (R == 8) dft8<FWD, APART>(v);
 }
 
 // Length-R DFTs whose upper inputs v[R/2 .. R-1] are zero (the first stage of
@@ -207,6 +219,16 @@ __device__ __forceinline__ void buf_store_cplx<double>(__amdgpu_buffer_rsrc_t r,
     __builtin_amdgcn_raw_buffer_store_b128(d, r, voff, soff, 0);
 }
 
+__device__ __forceinline__ void buf_store_real(__amdgpu_buffer_rsrc_t r, int voff, int soff, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, soff, 0);
+}
+__device__ __forceinline__ void buf_store_real(__amdgpu_buffer_rsrc_t r, int voff, int soff, double v) {
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    const unsigned long long a = (unsigned long long)__double_as_longlong(v);
+    const u2 d = {(unsigned)a, (unsigned)(a >> 32)};
+    __builtin_amdgcn_raw_buffer_store_b64(d, r, voff, soff, 0);
+}
+
 // The hardware hands consecutive workgroups of a launch to the eight XCDs in
 // turn, and each XCD has its own L2. Logical block index of workgroup b of nb
 // such that every XCD works through one contiguous range of logical blocks
@@ -248,8 +270,8 @@ __device__ __forceinline__ void stage_sync() {
 // x[b + r N/R], multiplies by exp(-/+ 2 pi i (b mod Ns) r / (Ns R)), applies
 // the length-R DFT and writes (b / Ns) Ns R + (b mod Ns) + r Ns.
 // HZ: elements N/2 .. N-1 of the input are zero (zero padding); the first
-// stage then never reads them (same values).
-template <typename T, int N, int E, bool FWD, int Ns, int R, bool HZ, bool WAVE, class Lay>
+// stage then never reads them (same values). APART: see dft8 (last stage).
+template <typename T, int N, int E, bool FWD, int Ns, int R, bool HZ, bool WAVE, bool APART, class Lay>
 __device__ __forceinline__ void fft_stage(cplx<T> (&reg)[E], cplx<T>* lds, Lay lay, int c, int j,
                                           const cplx<T>* __restrict__ tw, bool act) {
     constexpr int Tc = N / E;
@@ -281,7 +303,7 @@ __device__ __forceinline__ void fft_stage(cplx<T> (&reg)[E], cplx<T>* lds, Lay l
         if constexpr (first && HZ)
             dftR_hz<R, FWD>(v[q]);
         else
-            dftR<R, FWD>(v[q]);
+            dftR<R, FWD, APART && last>(v[q]);
     }
     if constexpr (last) {
 #pragma unroll
@@ -302,13 +324,13 @@ __device__ __forceinline__ void fft_stage(cplx<T> (&reg)[E], cplx<T>* lds, Lay l
     }
 }
 
-template <typename T, int N, int E, bool FWD, int Ns, bool HZ, bool WAVE, class Lay>
+template <typename T, int N, int E, bool FWD, int Ns, bool HZ, bool WAVE, bool APART, class Lay>
 __device__ __forceinline__ void fft_stages(cplx<T> (&reg)[E], cplx<T>* lds, Lay lay, int c, int j,
                                            const cplx<T>* __restrict__ tw, bool act) {
     if constexpr (Ns < N) {
         constexpr int R = cmin(cmin(8, E), N / Ns);
-        fft_stage<T, N, E, FWD, Ns, R, HZ, WAVE>(reg, lds, lay, c, j, tw, act);
-        fft_stages<T, N, E, FWD, Ns * R, HZ, WAVE>(reg, lds, lay, c, j, tw, act);
+        fft_stage<T, N, E, FWD, Ns, R, HZ, WAVE, APART>(reg, lds, lay, c, j, tw, act);
+        fft_stages<T, N, E, FWD, Ns * R, HZ, WAVE, APART>(reg, lds, lay, c, j, tw, act);
     }
 }
 
@@ -438,13 +460,13 @@ __device__ __forceinline__ void fft_regs_k(cplx<T> (&reg)[K][E], const cplx<T> (
 // WAVE: the N/E threads of each transform are consecutive lanes of one wave
 // and its LDS region is touched by no other wave, so the stages synchronise
 // within the wave only (see stage_sync).
-template <typename T, int N, int E, bool FWD, bool HZ = false, bool WAVE = false, class Lay>
+template <typename T, int N, int E, bool FWD, bool HZ = false, bool WAVE = false, bool APART = false, class Lay>
 __device__ __forceinline__ void fft_regs(cplx<T> (&reg)[E], cplx<T>* lds, Lay lay, int c, int j,
                                          const cplx<T>* __restrict__ tw, bool act = true) {
     static_assert(N % E == 0, "E must divide N");
     static_assert(!HZ || E >= 2, "a zero upper half needs two elements per thread");
     static_assert(!WAVE || (N / E <= 64 && 64 % (N / E) == 0), "a wave-local transform fits one wave");
-    fft_stages<T, N, E, FWD, 1, HZ, WAVE>(reg, lds, lay, c, j, tw, act);
+    fft_stages<T, N, E, FWD, 1, HZ, WAVE, APART>(reg, lds, lay, c, j, tw, act);
 }
 
 }  // namespace dds

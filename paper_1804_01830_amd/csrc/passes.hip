@@ -415,6 +415,28 @@ XLayout x_lds_layout(int M, int E, int elem_bytes) {
 }
 int x_lds_ld(int M, int E, int elem_bytes) { return x_lds_layout(M, E, elem_bytes).ld; }
 
+// Complex values of a lane transform's twiddle table (col_tw_count).
+static int col_tw(int Py) { return Py == 16 ? 8 : Py == 32 ? 24 : Py == 64 ? 56 : Py == 128 ? 120 : 192; }
+// Planes the fused x-y kernels take (row strides, rows per wave and tables as
+// in plane.hpp): half lengths 8 to 128, column lengths 16 to 128, and in FP32
+// 256 at half length 128, where the plane with its tables fits a CU's LDS.
+// The line lies there because a lane holds Py / 4 values: at 256 that is half
+// of a wave's registers, which pays only for planes that give a block eight
+// waves. One realisation, three channels, fused / separate, forward + inverse
+// in us: FP32 32x32x4 9.1 / 13.6, 64^3 22 / 31, 100x75x20 (256, M = 128) 34 /
+// 45 (the fused kernels before these), 30x100x20 (256, M = 32) 26 / 19 (not
+// taken); FP64 33x20x9 12 / 15, 64^3 38 / 48. Closest: periodic 64x128 rows,
+// two realisations, 22.4 / 23.0 (FP64 30.2 / 30.9).
+bool plane_fits(int Py, int M, int ny, int elem_bytes) {
+    const bool lengths = M >= 8 && M <= 128 && Py >= 16 && (Py <= 128 || (Py == 256 && M == 128 && elem_bytes == 4));
+    if (!lengths || ny < 1 || ny > Py) return false;
+    const int rpw = 64 / (M / (M >= 64 && elem_bytes == 4 ? 16 : 8));
+    const int ld = elem_bytes == 4 && M == 128 ? 152 : elem_bytes == 4 && M == 64 ? 76 : M + M / 8;
+    const int rows = (int)round_up(ny, rpw), rmax = ny <= Py / 2 ? Py / 2 : Py;
+    const size_t vals = (size_t)(rows < rmax ? rows + 4 : rows) * ld + std::max(Py, rpw) + col_tw(Py) + 2 * M + Py;
+    return vals * 2 * elem_bytes <= (size_t)160 * 1024;
+}
+
 // Real rows can be accessed in pairs when every row starts on a pair boundary.
 template <typename T>
 static int pairs_ok(const T* base, int64_t stride, int n) {

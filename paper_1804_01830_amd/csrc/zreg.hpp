@@ -8,51 +8,10 @@
 #pragma once
 
 #include "ddstress_internal.hpp"
+#include "lane_fft.hpp"
 #include "zfused.hpp"
 
 namespace dds {
-
-// Exchange lane bit LB with the register-index bit that distinguishes a (0)
-// from b (1): afterwards a lane whose bit is 1 holds in a what its partner
-// held in b, and a lane whose bit is 0 holds in b what its partner held in a.
-template <int LB>
-__device__ __forceinline__ void lane_swap(float& a, float& b) {
-    static_assert(LB >= 3 && LB <= 5, "lane bit");
-    const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
-    if constexpr (LB == 5) {
-        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-        a = __uint_as_float(r[0]);
-        b = __uint_as_float(r[1]);
-    } else if constexpr (LB == 4) {
-        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-        a = __uint_as_float(r[0]);
-        b = __uint_as_float(r[1]);
-    } else {
-        // lanes 8..15 of each row take b from lane - 8, lanes 0..7 take a from lane + 8
-        a = __uint_as_float((unsigned)__builtin_amdgcn_update_dpp((int)x, (int)y, 0x118, 0xf, 0xc, false));
-        b = __uint_as_float((unsigned)__builtin_amdgcn_update_dpp((int)y, (int)x, 0x108, 0xf, 0x3, false));
-    }
-}
-template <int LB>
-__device__ __forceinline__ void lane_swap(cplx<float>& a, cplx<float>& b) {
-    lane_swap<LB>(a.x, b.x);
-    lane_swap<LB>(a.y, b.y);
-}
-
-// exp(-2 pi i q / 16) for the products q of a radix-4 stage behind a radix-4
-// stage: the values of the twiddle table (the library's table holds the cosine
-// of the long double nearest to pi / 2 at q = 4, kept here so that every form
-// gives the same bits).
-template <int Q>
-__device__ __forceinline__ cplx<float> w16() {
-    constexpr float c1 = 0x1.d906bcp-1f, s1 = 0x1.87de2ap-2f, h = 0x1.6a09e6p-1f;
-    if constexpr (Q == 1) return {c1, -s1};
-    else if constexpr (Q == 2) return {h, -h};
-    else if constexpr (Q == 3) return {s1, -c1};
-    else if constexpr (Q == 4) return {-0x1.d9ccecp-66f, -1.0f};
-    else if constexpr (Q == 6) return {-h, -h};
-    else return {-c1, s1};                       // Q == 9
-}
 
 // Radix-4 DFT over registers v[I0 + r S], r = 0..3 (r >= 2 zero with HZ).
 template <bool FWD, bool HZ, int I0, int S, int E>
@@ -78,9 +37,9 @@ __device__ __forceinline__ void reg_dft4(cplx<float> (&v)[E]) {
 template <bool FWD, int K0, int I0, int S, int E>
 __device__ __forceinline__ void reg_stage16(cplx<float> (&v)[E]) {
     if constexpr (K0 > 0) {
-        v[I0 + S] = twmul<FWD>(v[I0 + S], w16<K0>());
-        v[I0 + 2 * S] = twmul<FWD>(v[I0 + 2 * S], w16<2 * K0>());
-        v[I0 + 3 * S] = twmul<FWD>(v[I0 + 3 * S], w16<3 * K0>());
+        v[I0 + S] = twmul<FWD>(v[I0 + S], wconst<16, K0, float>());
+        v[I0 + 2 * S] = twmul<FWD>(v[I0 + 2 * S], wconst<16, 2 * K0, float>());
+        v[I0 + 3 * S] = twmul<FWD>(v[I0 + 3 * S], wconst<16, 3 * K0, float>());
     }
     reg_dft4<FWD, false, I0, S>(v);
 }

@@ -18,7 +18,7 @@ def cache_path():
 
 
 # Part of every key: entries written for other launch-shape fields are not reused.
-LAYOUT = "z4"
+LAYOUT = "z5"
 
 
 def device_tag():
