@@ -10,9 +10,10 @@
 // layers rewritten from the real layers after each step (Eq. 18b and its
 // analogues), the total stress by Hooke's law with central differences.
 //
-// Kernels, all HBM-bound stencils: k_relax_load (f, surface terms, u = 0),
+// Kernels, all memory-bound stencils: k_relax_load (f, surface terms, u = 0),
 // k_relax_march (one explicit step into the other state buffer, marching
-// along z with LDS planes), k_relax_ghost (both ghost layers), k_relax_norm
+// along z with LDS planes, the ghost layers formed on the way), k_relax_ghost (both
+// ghost layers of the state that is handed out), k_relax_norm
 // (max |update| / dt), k_relax_stress.
 #include <algorithm>
 #include <cmath>
@@ -26,17 +27,6 @@ namespace dds {
 namespace {
 
 constexpr int kRelaxBX = 64, kRelaxBY = 4;
-// Tile of the z-marching step and the number of blocks its z chunks aim at.
-#ifndef DDS_RELAX_TX
-#define DDS_RELAX_TX 64
-#endif
-#ifndef DDS_RELAX_TY
-#define DDS_RELAX_TY 16
-#endif
-#ifndef DDS_RELAX_BLOCKS
-#define DDS_RELAX_BLOCKS 512
-#endif
-constexpr int kRelaxBlocks = DDS_RELAX_BLOCKS;
 constexpr int kRelaxMaxN = 4096;
 
 template <typename T>
@@ -147,105 +137,150 @@ __device__ __forceinline__ void ghost_value(const T* __restrict__ u, const T* __
 }
 
 // One explicit step, marching along z: a block owns a TX x TY tile of
-// columns and a chunk of node layers; the three displacement planes the
-// stencil touches (layers k - 1, k, k + 1, three components, one halo cell
-// on each side, periodic wrap) live in LDS in a rotating set of three slots,
-// and the next plane is fetched into registers while the current layer is
-// computed. Each displacement value is read from memory once per chunk
-// (plus halos and the two planes that chunks share); the blocks of one tile
-// take consecutive logical indices, which xcd_block keeps on one XCD. The
-// ghost planes are read like the others (a ghost pass follows every step:
-// evaluating them in the surface blocks instead puts their dependent loads
-// on the critical path and was slower).
-template <typename T, int TX, int TY>
+// columns and a chunk of node layers. Each displacement plane (three
+// components, one halo cell on each side, periodic wrap) passes through LDS
+// once, in one of two slots; what the stencil needs of it afterwards (the value and its x
+// and y differences, and for the layer in hand its second differences in the
+// plane) stays in registers, so a layer costs 27 LDS reads and one barrier. The next
+// plane and the next layer's force are requested before the arithmetic.
+//
+// The ghost planes are not read: the blocks of the surface chunks form theirs
+// from the real layers (Eq. 18b) while their first planes are on the way. For that
+// the last chunk marches downwards, so that a ghost plane is always a block's
+// first one (there are at least two chunks).
+template <typename T, int TX, int TY, bool STREAM>
 __global__ void __launch_bounds__(TX* TY)
-    k_relax_march(const T* __restrict__ u, T* __restrict__ un, const T* __restrict__ f, RelaxGeom<T> g, int tiles_x,
-                  int nchunks, int kc) {
+    k_relax_march(const T* __restrict__ u, T* __restrict__ un, const T* __restrict__ f, const T* __restrict__ phi,
+                  RelaxGeom<T> g, int tiles_x, int nchunks, int kc) {
     constexpr int W = TX + 2, H = TY + 2, PL = W * H;           // plane tile with halo
     constexpr int NT = TX * TY, PER = (PL + NT - 1) / NT;       // loads per thread per component
-    __shared__ T lds[3][3][PL];                                 // [slot][component][tile]
-    const int nb = gridDim.x;
-    const int lb = xcd_block(blockIdx.x, nb);
+    __shared__ T lds[2][3][PL];                                 // [slot][component][tile]
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
     const int chunk = lb % nchunks, tile = lb / nchunks;
     const int i0 = (tile % tiles_x) * TX, j0 = (tile / tiles_x) * TY;
-    const int k0 = chunk * kc;
-    const int k1 = min(g.nz, k0 + kc);
-    if (k0 >= k1) return;                                       // uniform per block
+    const int k0 = chunk * kc, n = min(g.nz, k0 + kc) - k0;     // node layers k0 .. k0 + n - 1
+    const bool down = chunk == nchunks - 1;
+    const int dir = down ? -1 : 1, kf = down ? k0 + n - 1 : k0; // first layer of the march
+    const T hz = down ? -g.hz : g.hz;
     const int t = threadIdx.x, tx = t % TX, ty = t / TX;
     const int i = i0 + tx, j = j0 + ty;
     const bool ok = i < g.nx && j < g.ny;
-    // global offsets (within one layer) of this thread's share of the halo tile
-    int64_t off[PER];
-    int slot_e[PER];
+    // offsets (within one layer) of this thread's share of the halo tile
+    int gi[PER], gj[PER];
+    uint32_t off[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const int e = t + q * NT;
-        slot_e[q] = e < PL ? e : -1;
-        const int ex = e % W, ey = e / W;
-        int gx = (i0 + ex - 1) % g.nx, gy = (j0 + ey - 1) % g.ny;
-        if (gx < 0) gx += g.nx;
-        if (gy < 0) gy += g.ny;
-        off[q] = (int64_t)gy * g.nx + gx;
+        int x = i0 + e % W - 1, y = j0 + e / W - 1;
+        x = x < 0 ? x + g.nx : x;
+        y = y < 0 ? y + g.ny : y;
+        gi[q] = x < g.nx ? x : x % g.nx;
+        gj[q] = y < g.ny ? y : y % g.ny;
+        off[q] = (uint32_t)gj[q] * (uint32_t)g.nx + (uint32_t)gi[q];
     }
-    T pre[3][PER];
-    auto fetch = [&](int layer) {
-        const int64_t lo = (int64_t)layer * g.plane;
+    using Plane = T[3][PER];
+    auto fetch = [&](Plane& pre, int layer) {
+        const T* src = u + layer * g.plane;
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
+        for (int q = 0; q < PER; ++q)
+            if (t + q * NT < PL)
 #pragma unroll
-            for (int q = 0; q < PER; ++q)
-                if (slot_e[q] >= 0) pre[c][q] = u[c * g.cstride + lo + off[q]];
+                for (int c = 0; c < 3; ++c) pre[c][q] = src[c * g.cstride + off[q]];
     };
-    auto store = [&](int layer) {
-        const int sl = layer % 3;
+    auto store = [&](const Plane& pre, int slot) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
+        for (int q = 0; q < PER; ++q)
+            if (t + q * NT < PL)
 #pragma unroll
-            for (int q = 0; q < PER; ++q)
-                if (slot_e[q] >= 0) lds[sl][c][slot_e[q]] = pre[c][q];
+                for (int c = 0; c < 3; ++c) lds[slot][c][t + q * NT] = pre[c][q];
+    };
+    const uint32_t node = ok ? (uint32_t)j * (uint32_t)g.nx + (uint32_t)i : 0;
+    auto fetch_force = [&](T (&r)[3], int k) {
+        const T* src = f + k * g.plane;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            r[a] = STREAM ? __builtin_nontemporal_load(src + a * g.fstride + node) : src[a * g.fstride + node];
     };
     const int ctr = (ty + 1) * W + tx + 1;
-    auto compute = [&](int k) {
-        if (!ok) return;
-        const int L = k + 1;
-        const int sd = (L - 1) % 3, sc = L % 3, su = (L + 1) % 3;
-        T dxx[3], dyy[3], dzz[3], dxy[3], dxz[3], dyz[3], u0[3];
+    struct Low { T c, dx, dy; } a[3], b[3];                     // layers k - dir and k: value, first differences
+    T xx[3], yy[3], xy[3];                                      // layer k: second differences in its plane
+    auto low = [&](int slot, Low (&r)[3]) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const T* lz = lds[sc][c];
-            const T* lu = lds[su][c];
-            const T* ld = lds[sd][c];
-            const T c0 = lz[ctr];
-            u0[c] = c0;
-            dxx[c] = (lz[ctr + 1] - T(2) * c0 + lz[ctr - 1]) * g.qx;
-            dyy[c] = (lz[ctr + W] - T(2) * c0 + lz[ctr - W]) * g.qy;
-            dzz[c] = (lu[ctr] - T(2) * c0 + ld[ctr]) * g.qz;
-            dxy[c] = ((lz[ctr + W + 1] - lz[ctr + W - 1]) * g.hx - (lz[ctr - W + 1] - lz[ctr - W - 1]) * g.hx) * g.hy;
-            dxz[c] = ((lu[ctr + 1] - lu[ctr - 1]) * g.hx - (ld[ctr + 1] - ld[ctr - 1]) * g.hx) * g.hz;
-            dyz[c] = ((lu[ctr + W] - lu[ctr - W]) * g.hy - (ld[ctr + W] - ld[ctr - W]) * g.hy) * g.hz;
-        }
-        const T gd[3] = {dxx[0] + dxy[1] + dxz[2], dxy[0] + dyy[1] + dyz[2], dxz[0] + dyz[1] + dzz[2]};
-        const int64_t n = (int64_t)k * g.plane + (int64_t)j * g.nx + i;
-        const int64_t o = n + g.plane;                          // the same node in the displacement layout
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const T lap = dxx[a] + dyy[a] + dzz[a];
-            const T v = (g.A - g.B) * gd[a] + g.B * lap + f[a * g.fstride + n];
-            un[a * g.cstride + o] = u0[a] + g.dt * v;
+            const T* l = lds[slot][c] + ctr;
+            r[c] = {l[0], (l[1] - l[-1]) * g.hx, (l[W] - l[-W]) * g.hy};
         }
     };
-    fetch(k0);
-    store(k0);
-    fetch(k0 + 1);
-    store(k0 + 1);
-    fetch(k0 + 2);
-    for (int k = k0; k < k1; ++k) {
-        const int L = k + 1;                                    // u layer of node layer k
-        store(L + 1);
+    auto second = [&](int slot) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const T* l = lds[slot][c] + ctr;
+            xx[c] = (l[1] - T(2) * l[0] + l[-1]) * g.qx;
+            yy[c] = (l[W] - T(2) * l[0] + l[-W]) * g.qy;
+            xy[c] = ((l[W + 1] - l[W - 1]) * g.hx - (l[-W + 1] - l[-W - 1]) * g.hx) * g.hy;
+        }
+    };
+    Plane pre;                                                  // the next plane and force
+    T fn[3];
+    {
+        Plane first, mid;
+        fetch(mid, kf + 1);
+        fetch(pre, kf + 1 + dir);
+        fetch_force(fn, kf);
+        if (down || chunk == 0) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                if (t + q * NT < PL) {
+                    T v[3];
+                    ghost_value(u, phi, g, down ? 1 : 0, gi[q], gj[q], v);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) first[c][q] = v[c];
+                }
+        } else {
+            fetch(first, kf + 1 - dir);
+        }
+        store(first, 0);
+        store(mid, 1);
+    }
+    __syncthreads();
+    low(0, a);
+    low(1, b);
+    second(1);
+    __syncthreads();                                            // slot 0 is refilled next
+    for (int m = 0; m < n; ++m) {
+        const int k = kf + dir * m;
+        store(pre, m & 1);
         __syncthreads();
-        if (k + 1 < k1) fetch(L + 2);                           // overlaps the arithmetic below
-        compute(k);
-        __syncthreads();                                        // slot (L - 1) % 3 is refilled next
+        const T fk[3] = {fn[0], fn[1], fn[2]};
+        if (m + 1 < n) {                                        // overlaps the arithmetic below
+            fetch(pre, k + 1 + 2 * dir);
+            fetch_force(fn, k + dir);
+        }
+        Low c[3];
+        low(m & 1, c);
+        T zz[3], xz[3], yz[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            zz[d] = (c[d].c - T(2) * b[d].c + a[d].c) * g.qz;
+            xz[d] = (c[d].dx - a[d].dx) * hz;
+            yz[d] = (c[d].dy - a[d].dy) * hz;
+        }
+        const T gd[3] = {xx[0] + xy[1] + xz[2], xy[0] + yy[1] + yz[2], xz[0] + yz[1] + zz[2]};
+        if (ok) {
+            T* dst = un + (k + 1) * g.plane;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T lap = xx[d] + yy[d] + zz[d];
+                const T v = (g.A - g.B) * gd[d] + g.B * lap + fk[d];
+                dst[d * g.cstride + node] = b[d].c + g.dt * v;
+            }
+        }
+        if (m + 1 < n) second(m & 1);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            a[d] = b[d];
+            b[d] = c[d];
+        }
     }
 }
 
@@ -417,26 +452,38 @@ struct ddstress_relax_s {
         check_hip(hipGetLastError(), "relaxation ghost launch");
         cur = 0;
     }
+    // One step from a into b, in z chunks so that about `target` blocks run.
+    template <typename T, int TX, int TY, bool STREAM>
+    void march(const T* a, T* b, const RelaxGeom<T>& g, int target, hipStream_t st) {
+        const int tiles_x = (desc.n[0] + TX - 1) / TX, tiles = tiles_x * ((desc.n[1] + TY - 1) / TY);
+        int nchunks = std::max(2, std::min(desc.n[2], (target + tiles - 1) / tiles));
+        const int kc = (desc.n[2] + nchunks - 1) / nchunks;
+        nchunks = (desc.n[2] + kc - 1) / kc;
+        hipLaunchKernelGGL((k_relax_march<T, TX, TY, STREAM>), dim3((unsigned)(tiles * nchunks)), dim3(TX * TY), 0, st, a,
+                           b, f.as<T>(), phi.as<T>(), g, tiles_x, nchunks, kc);
+        check_hip(hipGetLastError(), "relaxation step launch");
+    }
     template <typename T>
     void iterate(int n, hipStream_t st) {
         const RelaxGeom<T> g = make_geom<T>(desc, dt, A, B);
-        // z-marching tiles of TX x TY columns; z chunks so that about kRelaxBlocks blocks run
-        constexpr int TX = DDS_RELAX_TX, TY = DDS_RELAX_TY;
-        const int tiles_x = (desc.n[0] + TX - 1) / TX, tiles_y = (desc.n[1] + TY - 1) / TY;
-        const int tiles = tiles_x * tiles_y;
-        int nchunks = std::max(1, std::min(desc.n[2], (kRelaxBlocks + tiles - 1) / tiles));
-        const int kc = (desc.n[2] + nchunks - 1) / nchunks;
-        nchunks = (desc.n[2] + kc - 1) / kc;
-        const unsigned blocks = (unsigned)(tiles * nchunks);
+        // Tiles of 64 x 4 columns, or of 128 x 8 on large films that they fill exactly:
+        // those have less halo, but few blocks, so a ragged film leaves CUs idle. In us per step,
+        // 128 x 8 / 64 x 4: 256x256x64 28.7 / 30.5, 128x128x32 7.9 / 8.6, 200x180x40 22.1 / 15.9,
+        // 70x33x12 FP64 8.5 / 5.8. The force streams past the caches once a step touches more than
+        // the 256 MB that the last one holds: 256x256x64 FP64 68.3 against 72.9, FP32 (154 MB) 35.5 against 29.4.
+        const bool large = desc.n[0] % 128 == 0 && desc.n[1] % 8 == 0 && nodes() >= (int64_t(1) << 19);
+        const bool stream = (size_t)9 * nodes() * sizeof(T) > ((size_t)256 << 20);
         for (int s = 0; s < n; ++s) {
-            T* a = u[cur].as<T>();
+            const T* a = u[cur].as<T>();
             T* b = u[cur ^ 1].as<T>();
-            hipLaunchKernelGGL((k_relax_march<T, TX, TY>), dim3(blocks), dim3(TX * TY), 0, st, a, b, f.as<T>(), g,
-                               tiles_x, nchunks, kc);
-            check_hip(hipGetLastError(), "relaxation step launch");
-            hipLaunchKernelGGL((k_relax_ghost<T>), grid(2), dim3(kRelaxBX, kRelaxBY), 0, st, b, phi.as<T>(), g);
-            check_hip(hipGetLastError(), "relaxation ghost launch");
+            if (large) stream ? march<T, 128, 8, true>(a, b, g, 256, st) : march<T, 128, 8, false>(a, b, g, 256, st);
+            else stream ? march<T, 64, 4, true>(a, b, g, 1024, st) : march<T, 64, 4, false>(a, b, g, 1024, st);
             cur ^= 1;
+        }
+        if (n > 0) {                                            // the ghost layers of the last state only
+            hipLaunchKernelGGL((k_relax_ghost<T>), grid(2), dim3(kRelaxBX, kRelaxBY), 0, st, u[cur].as<T>(),
+                               phi.as<T>(), g);
+            check_hip(hipGetLastError(), "relaxation ghost launch");
         }
     }
     template <typename T>
