@@ -55,3 +55,31 @@ def test_fused_planes_give_the_bits_of_the_separate_passes(n, periodic, prec):
     assert torch.allclose(stats[0], stats[1], rtol=2e-12, atol=0)
     plan.close()
     other.close()
+
+
+@pytest.mark.parametrize("n", [(64, 64, 16), (20, 64, 16)])
+def test_many_double_planes_give_the_same_bits_every_time(n):
+    """Planes that share CUs (768 of them), whose wide stores have to wait."""
+    import torch
+    from paper_1804_01830_amd import binding as B
+    w = W.random_field(n, n_lines=1, batch=16, seed=62, d=(1.0, 1.0, 2.0))
+    desc = B.make_desc(w["n"], w["d"], w["mu"], w["nu"], w["lines"], precision=64, batch=16)
+    plan = B.Plan(desc)
+    i = plan.info()
+    t = B.Tuning()
+    t.rows_x, t.tk_y, t.ex, t.ey, t.tk_z, t.ez, t.z_groups = (i.rows_x, i.tile_y, i.ex, i.ey, i.tile_z, i.ez,
+                                                              i.z_groups)
+    t.yx = t.xy = 1
+    other = B.Plan(desc, tuning=t)
+    rho = torch.from_numpy(w["rho"]).to("cuda").contiguous()
+    ref, out = other.new_output(), plan.new_output()
+    other.set_density(rho)
+    other.stress(ref)
+    print(f"[fused planes] {n} FP64, 16 realisations, 20 evaluations", flush=True)
+    for _ in range(20):
+        plan.set_density(rho)
+        plan.stress(out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    plan.close()
+    other.close()
