@@ -161,7 +161,6 @@ __global__ void __launch_bounds__(TX* TY)
     const int k0 = chunk * kc, n = min(g.nz, k0 + kc) - k0;     // node layers k0 .. k0 + n - 1
     const bool down = chunk == nchunks - 1;
     const int dir = down ? -1 : 1, kf = down ? k0 + n - 1 : k0; // first layer of the march
-    const T hz = down ? -g.hz : g.hz;
     const int t = threadIdx.x, tx = t % TX, ty = t / TX;
     const int i = i0 + tx, j = j0 + ty;
     const bool ok = i < g.nx && j < g.ny;
@@ -202,22 +201,27 @@ __global__ void __launch_bounds__(TX* TY)
             r[a] = STREAM ? __builtin_nontemporal_load(src + a * g.fstride + node) : src[a * g.fstride + node];
     };
     const int ctr = (ty + 1) * W + tx + 1;
-    struct Low { T c, dx, dy; } a[3], b[3];                     // layers k - dir and k: value, first differences
-    T xx[3], yy[3], xy[3];                                      // layer k: second differences in its plane
+    // Layers k - dir and k: value and differences along x and y; layer k: second
+    // differences along x, y and both. Products that the sums below take into an
+    // FMA are kept apart from their factor (see there).
+    struct Low { T c, dx, dy; } a[3], b[3];
+    T xx[3], yy[3], xy[3];
     auto low = [&](int slot, Low (&r)[3]) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const T* l = lds[slot][c] + ctr;
-            r[c] = {l[0], (l[1] - l[-1]) * g.hx, (l[W] - l[-W]) * g.hy};
+            r[c] = {l[0], l[1] - l[-1], l[W] - l[-W]};
         }
     };
     auto second = [&](int slot) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const T* l = lds[slot][c] + ctr;
-            xx[c] = (l[1] - T(2) * l[0] + l[-1]) * g.qx;
-            yy[c] = (l[W] - T(2) * l[0] + l[-W]) * g.qy;
-            xy[c] = ((l[W + 1] - l[W - 1]) * g.hx - (l[-W + 1] - l[-W - 1]) * g.hx) * g.hy;
+            xx[c] = l[1] - T(2) * l[0] + l[-1];
+            yy[c] = l[W] - T(2) * l[0] + l[-W];
+            if (c == 0) xx[c] *= g.qx;
+            else yy[c] *= g.qy;
+            if (c < 2) xy[c] = fmad(l[W + 1] - l[W - 1], g.hx, -((l[-W + 1] - l[-W - 1]) * g.hx));
         }
     };
     Plane pre;                                                  // the next plane and force
@@ -247,12 +251,16 @@ __global__ void __launch_bounds__(TX* TY)
     low(1, b);
     second(1);
     __syncthreads();                                            // slot 0 is refilled next
+    // Every product and sum is rounded as in
+    //   d2[c] = (next - 2 u + previous) q,  d2[c][d] = ((..) h - (..) h) h',
+    //   v = (A - B) grad div u + B laplacian u + f
+    // with the FMAs that contraction made of these formulas on one node at a time.
     for (int m = 0; m < n; ++m) {
         const int k = kf + dir * m;
         store(pre, m & 1);
         __syncthreads();
         const T fk[3] = {fn[0], fn[1], fn[2]};
-        if (m + 1 < n) {                                        // overlaps the arithmetic below
+        if (m + 1 < n) {                                    // overlaps the arithmetic below
             fetch(pre, k + 1 + 2 * dir);
             fetch_force(fn, k + dir);
         }
@@ -260,19 +268,21 @@ __global__ void __launch_bounds__(TX* TY)
         low(m & 1, c);
         T zz[3], xz[3], yz[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            zz[d] = (c[d].c - T(2) * b[d].c + a[d].c) * g.qz;
-            xz[d] = (c[d].dx - a[d].dx) * hz;
-            yz[d] = (c[d].dy - a[d].dy) * hz;
+        for (int d = 0; d < 3; ++d) {                       // (uniform selects)
+            zz[d] = (down ? a[d].c : c[d].c) - T(2) * b[d].c + (down ? c[d].c : a[d].c);
+            if (d != 1) xz[d] = fmad(down ? a[d].dx : c[d].dx, g.hx, -((down ? c[d].dx : a[d].dx) * g.hx));
+            if (d != 0) yz[d] = fmad(down ? a[d].dy : c[d].dy, g.hy, -((down ? c[d].dy : a[d].dy) * g.hy));
         }
-        const T gd[3] = {xx[0] + xy[1] + xz[2], xy[0] + yy[1] + yz[2], xz[0] + yz[1] + zz[2]};
+        const T gd[3] = {fmad(xz[2], g.hz, fmad(xy[1], g.hy, xx[0])), fmad(yz[2], g.hz, fmad(xy[0], g.hy, yy[1])),
+                         fmad(zz[2], g.qz, fmad(xz[0], g.hz, yz[1] * g.hz))};
+        const T lap[3] = {fmad(zz[0], g.qz, fmad(yy[0], g.qy, xx[0])), fmad(zz[1], g.qz, fmad(xx[1], g.qx, yy[1])),
+                          fmad(zz[2], g.qz, fmad(xx[2], g.qx, yy[2]))};
         if (ok) {
             T* dst = un + (k + 1) * g.plane;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const T lap = xx[d] + yy[d] + zz[d];
-                const T v = (g.A - g.B) * gd[d] + g.B * lap + fk[d];
-                dst[d * g.cstride + node] = b[d].c + g.dt * v;
+                const T v = fmad(g.B, lap[d], (g.A - g.B) * gd[d]) + fk[d];
+                dst[d * g.cstride + node] = fmad(g.dt, v, b[d].c);
             }
         }
         if (m + 1 < n) second(m & 1);
