@@ -349,7 +349,8 @@ constexpr int tw_count(int N, int E, int Ns = 1) {
                          tw_count(N, E, Ns * cmin(cmin(8, E), N / Ns));
 }
 
-template <typename T, int N, int E, int Ns, int K, int TWC>
+// PAIRED: see dft4_paired; the third twiddle of a radix-4 stage is W_4Ns^(k + Ns).
+template <typename T, int N, int E, int Ns, int K, int TWC, bool PAIRED = false>
 __device__ __forceinline__ void load_tw_stages(cplx<T> (&w)[TWC], int j, const cplx<T>* __restrict__ tw) {
     if constexpr (Ns < N) {
         constexpr int R = cmin(cmin(8, E), N / Ns);
@@ -360,13 +361,38 @@ __device__ __forceinline__ void load_tw_stages(cplx<T> (&w)[TWC], int j, const c
             for (int q = 0; q < NB; ++q) {
                 const int k = (j + Tc * q) & (Ns - 1);
 #pragma unroll
-                for (int r = 1; r < R; ++r) w[K + q * (R - 1) + r - 1] = tw[k * r * (N / (Ns * R))];
+                for (int r = 1; r < R; ++r)
+                    w[K + q * (R - 1) + r - 1] = tw[(PAIRED && r == 3 ? k + Ns : k * r) * (N / (Ns * R))];
             }
-            load_tw_stages<T, N, E, Ns * R, K + NB * (R - 1)>(w, j, tw);
+            load_tw_stages<T, N, E, Ns * R, K + NB * (R - 1), TWC, PAIRED>(w, j, tw);
         } else {
-            load_tw_stages<T, N, E, Ns * R, K>(w, j, tw);
+            load_tw_stages<T, N, E, Ns * R, K, TWC, PAIRED>(w, j, tw);
         }
     }
+}
+
+// A radix-4 stage formed as two radix-2 stages: four inputs b + r N/4 hold two
+// butterflies of each, so only the second's outputs travel, and the products
+// and their bits are those of a transform of radix-2 stages. w[0] = W_4Ns^k, w[1] =
+// W_2Ns^k, w[2] = W_4Ns^(k + Ns); in the first stage k = 0 and w2 is the last one.
+template <bool FWD, bool FIRST, bool HZ, typename T>
+__device__ __forceinline__ void dft4_paired(cplx<T>* v, const cplx<T>* w, cplx<T> w2) {
+    cplx<T> y[4];
+    if constexpr (FIRST && HZ) {
+        y[0] = y[1] = v[0];
+        y[2] = y[3] = v[1];
+    } else {
+        const cplx<T> b0 = FIRST ? v[2] : twmul<FWD>(v[2], w[1]), b1 = FIRST ? v[3] : twmul<FWD>(v[3], w[1]);
+        y[0] = cadd(v[0], b0);
+        y[1] = csub(v[0], b0);
+        y[2] = cadd(v[1], b1);
+        y[3] = csub(v[1], b1);
+    }
+    const cplx<T> c0 = FIRST ? y[2] : twmul<FWD>(y[2], w[0]), c1 = twmul<FWD>(y[3], w2);
+    v[0] = cadd(y[0], c0);
+    v[2] = csub(y[0], c0);
+    v[1] = cadd(y[1], c1);
+    v[3] = csub(y[1], c1);
 }
 
 // K transforms of length N taken through the stages together, with the
@@ -375,9 +401,10 @@ __device__ __forceinline__ void load_tw_stages(cplx<T> (&w)[TWC], int j, const c
 // regions lds + k * region. HZ: inputs m >= E/2 of every transform are zero
 // (zero-padded data) and are not read. Threads with act == false (whole
 // waves) take part in the barriers without touching LDS or computing.
-template <typename T, int N, int E, bool FWD, bool HZ, int Ns, int R, int KT, int K, int TWC, bool WAVE, class Lay>
+template <typename T, int N, int E, bool FWD, bool HZ, int Ns, int R, int KT, int K, int TWC, bool WAVE, bool PAIRED,
+          class Lay>
 __device__ __forceinline__ void fftk_stage(cplx<T> (&reg)[K][E], const cplx<T> (&w)[TWC], cplx<T>* lds, int region,
-                                           Lay lay, int c, int j, bool act) {
+                                           Lay lay, int c, int j, bool act, cplx<T> w4) {
     constexpr int Tc = N / E;
     constexpr int NB = E / R;
     constexpr bool first = (Ns == 1);
@@ -406,6 +433,11 @@ __device__ __forceinline__ void fftk_stage(cplx<T> (&reg)[K][E], const cplx<T> (
         for (int k = 0; k < K; ++k)
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
+                if constexpr (PAIRED && R == 4) {
+                    if constexpr (first) dft4_paired<FWD, true, HZ>(v[k][q], w, w4);
+                    else dft4_paired<FWD, false, false>(v[k][q], w + KT + q * 3, w[KT + q * 3 + 2]);
+                    continue;
+                }
                 if constexpr (!first) {
 #pragma unroll
                     for (int r = 1; r < R; ++r) v[k][q][r] = twmul<FWD>(v[k][q][r], w[KT + q * (R - 1) + r - 1]);
@@ -437,14 +469,14 @@ __device__ __forceinline__ void fftk_stage(cplx<T> (&reg)[K][E], const cplx<T> (
     }
 }
 
-template <typename T, int N, int E, bool FWD, bool HZ, int Ns, int KT, int K, int TWC, bool WAVE, class Lay>
+template <typename T, int N, int E, bool FWD, bool HZ, int Ns, int KT, int K, int TWC, bool WAVE, bool PAIRED, class Lay>
 __device__ __forceinline__ void fftk_stages(cplx<T> (&reg)[K][E], const cplx<T> (&w)[TWC], cplx<T>* lds, int region,
-                                            Lay lay, int c, int j, bool act) {
+                                            Lay lay, int c, int j, bool act, cplx<T> w4) {
     if constexpr (Ns < N) {
         constexpr int R = cmin(cmin(8, E), N / Ns);
-        fftk_stage<T, N, E, FWD, HZ, Ns, R, KT, K, TWC, WAVE>(reg, w, lds, region, lay, c, j, act);
-        fftk_stages<T, N, E, FWD, HZ, Ns * R, (Ns == 1 ? KT : KT + (E / R) * (R - 1)), K, TWC, WAVE>(
-            reg, w, lds, region, lay, c, j, act);
+        fftk_stage<T, N, E, FWD, HZ, Ns, R, KT, K, TWC, WAVE, PAIRED>(reg, w, lds, region, lay, c, j, act, w4);
+        fftk_stages<T, N, E, FWD, HZ, Ns * R, (Ns == 1 ? KT : KT + (E / R) * (R - 1)), K, TWC, WAVE, PAIRED>(
+            reg, w, lds, region, lay, c, j, act, w4);
     }
 }
 
@@ -454,7 +486,16 @@ template <typename T, int N, int E, bool FWD, bool HZ, int K, int TWC, bool WAVE
 __device__ __forceinline__ void fft_regs_k(cplx<T> (&reg)[K][E], const cplx<T> (&w)[TWC], cplx<T>* lds, int region,
                                            Lay lay, int c, int j, bool act = true) {
     static_assert(N % E == 0, "E must divide N");
-    fftk_stages<T, N, E, FWD, HZ, 1, 0, K, TWC, WAVE>(reg, w, lds, region, lay, c, j, act);
+    fftk_stages<T, N, E, FWD, HZ, 1, 0, K, TWC, WAVE, false>(reg, w, lds, region, lay, c, j, act, w[0]);
+}
+
+// The same with radix-4 stages as pairs of radix-2 stages (see dft4_paired);
+// w from load_tw_stages<..., true>, w4 the table's W_4.
+template <typename T, int N, int E, bool FWD, bool HZ, int TWC, class Lay>
+__device__ __forceinline__ void fft_paired(cplx<T> (&reg)[1][E], const cplx<T> (&w)[TWC], cplx<T> w4, cplx<T>* lds,
+                                           Lay lay, int c, int j) {
+    static_assert(E == 4 && N % E == 0, "four elements per thread");
+    fftk_stages<T, N, E, FWD, HZ, 1, 0, 1, TWC, true, true>(reg, w, lds, 0, lay, c, j, true, w4);
 }
 
 // Full transform of length N on the register distribution described above.

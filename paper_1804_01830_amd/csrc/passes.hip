@@ -209,9 +209,13 @@ int z_max_threads(int groups) { return groups == 1 ? 512 : 768; }
 bool z_groups_ok(int groups, int C) { return groups == 1 || groups == C; }
 // Many realisations amortise the grouped form's larger blocks; it is the
 // default from 16 realisations on, where one column per group fits a block
-// (threads and LDS) and the register form does not apply.
+// (threads and LDS) and neither the register form nor FP64's wave form applies
+// (wave / grouped, 16 realisations, us: three channels 64x64x16 95 / 177, 60x30x20
+// 76 / 216; six 64x64x16 183 / 245, 128x64x32 670 / 950, but 9x9x9 35 / 29, 9x9x5 29 / 22: not
+// taken below length 32).
 int default_z_groups(int N, int C, int B, int elem_bytes) {
     if (B < 16 || (elem_bytes == 4 && z_reg_applies(N, C, B))) return 1;
+    if (elem_bytes == 8 && N <= 128 && (C == 3 ? N >= 8 : C == 6 && N >= 32)) return 1;
     const int ev = default_ev_z(N, C, elem_bytes);
     const int e = N < ev ? N : ev;
     const bool fits = z_threads(N, C, 1, e) <= z_max_threads(C) && z_lds_bytes(N, 1, C, C, elem_bytes) <= 64 * 1024;
@@ -268,6 +272,23 @@ size_t z_wave_lds_bytes(int N, int C, int nkz, int B) {
     return (z_stage_bytes(kZWaveTile, C, nkz, 4) + 15) / 16 * 16 + (size_t)wpb * N * kZWaveTile * 8;
 }
 
+// The wave form with four elements per thread: one thread group of the base
+// class on tiles of 256 / N columns (one wave), z lengths 8 to 128, three or six
+// channels. FP64 takes it whatever the batch, FP32 for one or two realisations:
+// more are served better by the register form or the single-group form's staged
+// spectrum, and at length 128 six channels run out of registers. us, wave /
+// single-group form. FP32, three channels: 128x128x32 with 1, 2, 3 realisations 27 / 39,
+// 47 / 52, 101 / 84; 64^3 22 / 29, 37 / 43; 33x20x9 6.8 / 7.5, 8.0 / 11.6; six: 128x128x32 57 / 60,
+// 110 / 115, 70x50x16 14.5 / 20, 24 / 35, 20x14x10 8.0 / 8.6, 8.7 / 15.2, 256x256x64 (length
+// 128) 730 / 500. FP64, three channels: 128x128x32 with 1, 2, 8 realisations 50 / 90,
+// 113 / 150, 400 / 515; 64^3 36 / 57; 33x20x9 with 1, 2, 5 8.4 / 9.5, 11.6 / 16, 21 / 29; six:
+// 128x128x32 123 / 141, 70x50x16 with 3 61 / 125.
+bool z_wave4_applies(int N, int C, int B, int ev, int tk, int elem_bytes) {
+    if (ev != base_ev_z(elem_bytes) || N < 8 || N > 128 || C > 6 || tk != 256 / N) return false;
+    return elem_bytes == 8 || (B <= 2 && (C == 3 || N <= 64));
+}
+int z_wave4_waves(int B) { return B >= 4 ? 4 : B >= 2 ? 2 : 1; }
+
 // The base class, or the smallest larger one with which a block of one
 // column per group fits.
 int default_ev_z(int N, int groups, int elem_bytes) {
@@ -299,6 +320,10 @@ int default_rows(int M, int elem_bytes) {
 
 int default_z_tk(int N, int C, int groups, int B, int elem_bytes) {
     if (elem_bytes == 4 && groups == 1 && z_reg_applies(N, C, B)) return z_reg_tile(N);
+    // (length 8 in FP64: one realisation 5.9 us against 5.3 in the single-group form, four 8.4 / 12.3)
+    if (groups == 1 && z_wave4_applies(N, C, B, base_ev_z(elem_bytes), 256 / N, elem_bytes) &&
+        !(elem_bytes == 8 && N == 8 && B == 1))
+        return 256 / N;
     const int tc = N / ecount(N, default_ev_z(N, groups, elem_bytes));
     int tk;
     if (groups != 1) {
@@ -548,7 +573,8 @@ void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, 
     // tiles x ky rows; in place of the Nyquist strip's tile, its groups x realisations
     // the register form takes over wherever its tile and enough realisations are given
     const bool reg = sizeof(T) == 4 && groups == 1 && ev == 4 && z_reg_applies(N, g.C, g.B) && tk == z_reg_tile(N);
-    g.sb = reg ? z_reg_waves(g.B) : 1;
+    const bool wave4 = groups == 1 && !reg && z_wave4_applies(N, g.C, g.B, ev, tk, (int)sizeof(T));
+    g.sb = reg ? z_reg_waves(g.B) : wave4 ? z_wave4_waves(g.B) : 1;
     const int64_t blocks = g.nyq > 0 ? (int64_t)(g.ntiles - 1) * g.nky + (int64_t)g.nyq * ((g.B + g.sb - 1) / g.sb)
                                      : (int64_t)g.ntiles * g.nky;
     if (blocks <= 0) return;

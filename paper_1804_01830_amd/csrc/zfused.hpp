@@ -399,14 +399,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
 
 
 // ----------------------------------------------------------------------------
-// Fused z pass, wave form (FP32, z length 64, 8 elements per thread). A block
-// owns TK = 8 consecutive kx columns at one ky (or a group of the Nyquist
-// strip, see z_roles), stages their spectrum tile in
-// LDS once (as the single-group form does) and runs WPB waves; wave w
-// evaluates realisations b = w, w + WPB, ... on its own. Its 64 lanes hold the
-// 8 columns with 8 lanes each (lane = 8 j + c: rows j + 8 m of column c), so
-// a wave load or store covers 8 rows of 64 contiguous bytes, and every
-// transform's lanes are in the wave: the stages exchange through a
+// Fused z pass, wave form. A block owns TK = 64 E / N consecutive kx columns at
+// one ky (or a group of the Nyquist strip, see z_roles) and runs RW waves; wave
+// w evaluates realisations b = w, w + RW, ... on its own. Its 64 lanes hold the
+// TK columns with N / E lanes each (lane = TK j + c: rows j + (N / E) m of column
+// c), so every transform's lanes are in the wave: the stages exchange through a
 // wave-private LDS region and synchronise within the wave (no workgroup
 // barrier after the staging). Per realisation the C density columns are
 // transformed along z (rows z >= N/2 are padding and are not loaded) and kept
@@ -414,16 +411,26 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
 //     sigma^_v(k) = sum_c i S_{v,c}(k) rho^_c(k)      (K^ = i S, K odd),
 // summed over c in increasing order, is transformed back along z and rows
 // z < nz are written. The next realisation's density is requested before the
-// inverse transforms. The radix sequence (8, 8) differs from the other forms'
-// (4, 4, 4), so results agree with them to rounding, not bit for bit.
+// inverse transforms.
+// SL: the block stages its spectrum tile in LDS once (as the single-group form
+// does). Otherwise a component's values come from memory, requested before the
+// inverse transform of the component before it.
+//
+// Holding C channels instead of six accumulators leaves registers for four
+// elements per thread in FP64, half the exchanges of the single-group form's
+// two, and neither barriers nor the spills that four accumulated elements
+// cost it: its LDS traffic was half of its time. One realisation, three channels,
+// 128 x 128 x 32 FP64 50 us (single-group form 90), FP32 27 (39); 64^3 FP64 36 (57):
+// 231 MB in 50 us, 4.6 TB/s within the 256 MB cache.
+// Eight elements: 57 and 41 us (FP64). With E = 4 the stages are the
+// single-group form's and so are the bits: radix 4 in FP32, pairs of radix 2 in
+// FP64 (see dft4_paired); with E = 8 (8, 8) results agree to rounding.
 // ----------------------------------------------------------------------------
-template <typename T, int N, int E, int NC, int WPB>
-__global__ void __launch_bounds__(64 * WPB) k_z_wave(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out,
+template <typename T, int N, int E, int NC, int RW, bool SL>
+__global__ void __launch_bounds__(64 * RW) k_z_wave(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out,
                                                      const T* __restrict__ spec, ZGeom g,
                                                      const cplx<T>* __restrict__ tw) {
-    constexpr int TK = kZWaveTile;
-    constexpr int Tc = N / E;
-    static_assert(Tc * TK == 64, "the tile's columns fill one wave");
+    constexpr int Tc = N / E, TK = 64 / Tc;                     // lanes per column, columns
     constexpr int EH = (E + 1) / 2;        // elements that can hold data rows (z < N/2)
     constexpr bool HZ = true;              // the upper half of every input column is padding
     constexpr int KS = (6 * NC + 1) * TK;  // staged row stride (values)
@@ -444,7 +451,7 @@ __global__ void __launch_bounds__(64 * WPB) k_z_wave(const cplx<T>* __restrict__
     const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)g.C * 6 * nkz * TK;
     const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * TK * sizeof(T)));
     T* s_l = reinterpret_cast<T*>(smem_raw);
-    const size_t stage_bytes = ((size_t)nkz * KS * sizeof(T) + 15) / 16 * 16;
+    const size_t stage_bytes = SL ? ((size_t)nkz * KS * sizeof(T) + 15) / 16 * 16 : 0;
     cplx<T>* xw = reinterpret_cast<cplx<T>*>(smem_raw + stage_bytes) + w * (N * TK);    // this wave's exchanges
     const ColMajor lay{TK};
     // density rows z < nz (rows >= nz read zero; lanes without data read a
@@ -465,10 +472,18 @@ __global__ void __launch_bounds__(64 * WPB) k_z_wave(const cplx<T>* __restrict__
             for (int m = 0; m < EH; ++m) nxt[ch][m] = buf_cplx<T>(rr, r_off[m], m * r_step);
         }
     };
-    if (ro.b0 + w < ro.b1) load_rho(ro.b0 + w);
+    constexpr bool AHEAD = sizeof(T) * NC <= 24;                // registers for the next realisation's density
+    if (AHEAD && ro.b0 + w < ro.b1) load_rho(ro.b0 + w);
     constexpr int TWC = tw_count(N, E) > 0 ? tw_count(N, E) : 1;
     cplx<T> twr[TWC];
-    load_tw_stages<T, N, E, 1, 0, TWC>(twr, j, tw + (N - 1));
+    constexpr bool PAIRED = sizeof(T) == 8;                      // (the radix-2 stages of FP64)
+    load_tw_stages<T, N, E, 1, 0, TWC, PAIRED>(twr, j, tw + (N - 1));
+    const cplx<T> w4 = tw[(N - 1) + N / 4];
+    const auto fft = [&](auto fwd, cplx<T> (&v)[1][E]) {
+        constexpr bool F = decltype(fwd)::value;
+        if constexpr (PAIRED) fft_paired<T, N, E, F, F && HZ, TWC>(v, twr, w4, xw, lay, c, j);
+        else fft_regs_k<T, N, E, F, F && HZ, 1, TWC, true>(v, twr, xw, 0, lay, c, j);
+    };
     // staged row of each element (see the single-group form)
     int s_row[E];
 #pragma unroll
@@ -479,18 +494,39 @@ __global__ void __launch_bounds__(64 * WPB) k_z_wave(const cplx<T>* __restrict__
             asm volatile("" : "+v"(s_row[m]));
         }
     }
-    stage_spectrum_tile<T, NC, TK, 64 * WPB>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x);
-    __syncthreads();
+    if constexpr (SL) {
+        stage_spectrum_tile<T, NC, TK, 64 * RW>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x);
+        __syncthreads();
+    }
+    // unstaged: a component's values, requested one component ahead
+    const int s_lane = (j * TK + c) * (int)sizeof(T), s_lane_m = ((Tc - j) * TK + c) * (int)sizeof(T);
+    T sm[SL ? 1 : NC][E];
+    auto load_spec = [&](int v) {
+        if constexpr (!SL) {
+            int rows = nkz;
+            if constexpr (sizeof(T) == 4 || NC == 6) asm volatile("" : "+s"(rows));   // (its multiples are not kept)
+#pragma unroll
+            for (int ch = 0; ch < NC; ++ch)
+#pragma unroll
+                for (int m = 0; m < E; ++m) {
+                    const bool mir = zc && 2 * m >= E;              // uniform: selects, no branch
+                    sm[ch][m] = buf_real<T>(srs, mir ? s_lane_m : s_lane,
+                                            ((ch * 6 + v) * rows + (mir ? Tc * (E - 1 - m) : Tc * m)) * TK * (int)sizeof(T));
+                }
+        }
+    };
+    load_spec(0);
 
-    for (int b = ro.b0 + w; b < ro.b1; b += WPB) {
+    for (int b = ro.b0 + w; b < ro.b1; b += RW) {
+        if (!AHEAD) load_rho(b);
         cplx<T> rho[NC][1][E];
 #pragma unroll
         for (int ch = 0; ch < NC; ++ch) {
 #pragma unroll
             for (int m = 0; m < EH; ++m) rho[ch][0][m] = nxt[ch][m];
-            fft_regs_k<T, N, E, true, HZ, 1, TWC, true>(rho[ch], twr, xw, 0, lay, c, j);
+            fft(std::true_type{}, rho[ch]);
         }
-        if (b + WPB < ro.b1) load_rho(b + WPB);
+        if (AHEAD && b + RW < ro.b1) load_rho(b + RW);
 #pragma unroll
         for (int v = 0; v < 6; ++v) {
             cplx<T> acc[1][E];
@@ -498,16 +534,18 @@ __global__ void __launch_bounds__(64 * WPB) k_z_wave(const cplx<T>* __restrict__
             for (int m = 0; m < E; ++m) acc[0][m] = {T(0), T(0)};
 #pragma unroll
             for (int ch = 0; ch < NC; ++ch) {
-                const uint32_t mz = sign_mask(zc && ((g.sgn_z >> (ch * 6 + v)) & 1));   // staged values carry the y sign
+                const uint32_t mz = sign_mask(zc && ((g.sgn_z >> (ch * 6 + v)) & 1));
+                const uint32_t my = sign_mask(!SL && flip_y && ((g.sgn_y >> (ch * 6 + v)) & 1));   // (staged: applied)
 #pragma unroll
                 for (int m = 0; m < E; ++m) {
-                    const T sv = s_l[s_row[m] + (ch * 6 + v) * TK];
+                    const T sv = SL ? s_l[s_row[m] + (ch * 6 + v) * TK] : flip_sign(sm[SL ? 0 : ch][m], my);
                     const T sval = 2 * m >= E ? flip_sign(sv, mz) : sv;
                     acc[0][m].x -= sval * rho[ch][0][m].y;
                     acc[0][m].y += sval * rho[ch][0][m].x;
                 }
             }
-            fft_regs_k<T, N, E, false, false, 1, TWC, true>(acc, twr, xw, 0, lay, c, j);
+            if (v < 5 || b + RW < ro.b1) load_spec((v + 1) % 6);
+            fft(std::false_type{}, acc);
             if (nq.own) {
                 cplx<T>* dst = out_b + (int64_t)(b * 6 + v) * g.oqs;
 #pragma unroll
@@ -700,11 +738,11 @@ static void z_launch(int64_t blocks, int tk, const cplx<T>* in, cplx<T>* out, co
         const size_t lw = stage + (size_t)wpb * L * kZWaveTile * sizeof(cplx<T>);
         const dim3 grid((unsigned)blocks);
         if (wpb == 4)
-            hipLaunchKernelGGL((k_z_wave<T, L, E, NC, 4>), grid, dim3(256), lw, s, in, out, spec, g, tw);
+            hipLaunchKernelGGL((k_z_wave<T, L, E, NC, 4, true>), grid, dim3(256), lw, s, in, out, spec, g, tw);
         else if (wpb == 2)
-            hipLaunchKernelGGL((k_z_wave<T, L, E, NC, 2>), grid, dim3(128), lw, s, in, out, spec, g, tw);
+            hipLaunchKernelGGL((k_z_wave<T, L, E, NC, 2, true>), grid, dim3(128), lw, s, in, out, spec, g, tw);
         else
-            hipLaunchKernelGGL((k_z_wave<T, L, E, NC, 1>), grid, dim3(64), lw, s, in, out, spec, g, tw);
+            hipLaunchKernelGGL((k_z_wave<T, L, E, NC, 1, true>), grid, dim3(64), lw, s, in, out, spec, g, tw);
         (void)tk;
     } else if constexpr (GROUPED) {
         if constexpr (NC > 3 && L / E <= 64 && 64 % (L / E) == 0) {
@@ -720,12 +758,14 @@ static void z_launch(int64_t blocks, int tk, const cplx<T>* in, cplx<T>* out, co
         if (z_stage_spec(L, tk, NC, g.nkz_s, g.B, (int)sizeof(T))) {
             lds += z_stage_bytes(tk, NC, g.nkz_s, (int)sizeof(T));
             const dim3 grid((unsigned)blocks);
-            if (tk == 4)
-                hipLaunchKernelGGL((k_z_serial<T, L, E, NC, 4>), grid, block, lds, s, in, out, spec, g, tw, tk, ld);
-            else if (tk == 8)
-                hipLaunchKernelGGL((k_z_serial<T, L, E, NC, 8>), grid, block, lds, s, in, out, spec, g, tw, tk, ld);
-            else
-                hipLaunchKernelGGL((k_z_serial<T, L, E, NC, 16>), grid, block, lds, s, in, out, spec, g, tw, tk, ld);
+            const auto staged = [&](auto tkc) {
+                constexpr int TK = decltype(tkc)::value;
+                if constexpr (!(sizeof(T) == 8 && E == 2 && L >= 8 && L <= 128 && TK * L == 256))   // (the wave form)
+                    hipLaunchKernelGGL((k_z_serial<T, L, E, NC, TK>), grid, block, lds, s, in, out, spec, g, tw, tk, ld);
+            };
+            if (tk == 4) staged(std::integral_constant<int, 4>{});
+            else if (tk == 8) staged(std::integral_constant<int, 8>{});
+            else staged(std::integral_constant<int, 16>{});
         } else {
             hipLaunchKernelGGL((k_z_serial<T, L, E, NC, 0>), dim3((unsigned)blocks), block, lds, s, in, out, spec, g,
                                tw, tk, ld);
@@ -760,6 +800,27 @@ static void z_ev_long(int N, const cplx<T>* in, cplx<T>* out, const T* spec, con
     }
 }
 
+// The wave form with four elements per thread (see z_wave4_applies).
+template <typename T, int N, int NC>
+static void z_wave4(int64_t blocks, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& g, const cplx<T>* tw,
+                    hipStream_t s) {
+    constexpr bool SL = sizeof(T) == 8 && NC == 3;             // with several realisations
+    constexpr size_t x = (size_t)256 * sizeof(cplx<T>);       // exchange region of a wave: N x 256 / N
+    const size_t stage = SL ? (z_stage_bytes(256 / N, NC, g.nkz_s, (int)sizeof(T)) + 15) / 16 * 16 : 0;
+    const dim3 grid((unsigned)blocks);
+    const int rw = z_wave4_waves(g.B);
+    if (rw == 4) {
+        if constexpr (sizeof(T) == 8)
+            hipLaunchKernelGGL((k_z_wave<T, N, 4, NC, 4, SL>), grid, dim3(256), stage + 4 * x, s, in, out, spec, g, tw);
+        else
+            fail(DDSTRESS_E_INVALID, "the FP32 wave form takes at most two realisations");
+    } else if (rw == 2) {
+        hipLaunchKernelGGL((k_z_wave<T, N, 4, NC, 2, SL>), grid, dim3(128), stage + 2 * x, s, in, out, spec, g, tw);
+    } else {
+        hipLaunchKernelGGL((k_z_wave<T, N, 4, NC, 1, false>), grid, dim3(64), x, s, in, out, spec, g, tw);
+    }
+}
+
 template <typename T, int NC, bool GROUPED>
 void z_dispatch(int N, int ev, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& g,
                        const cplx<T>* tw, int tk, int64_t blocks, hipStream_t s) {
@@ -768,6 +829,17 @@ void z_dispatch(int N, int ev, const cplx<T>* in, cplx<T>* out, const T* spec, c
         if (N == 64 && ev == 8) {
             z_launch<T, 64, 8, NC, false>(blocks, tk, in, out, spec, g, tw, s);
             return;
+        }
+    }
+    if constexpr (!GROUPED && NC <= 6) {
+        if (z_wave4_applies(N, NC, g.B, ev, tk, (int)sizeof(T))) {
+            switch (N) {
+                case 8: z_wave4<T, 8, NC>(blocks, in, out, spec, g, tw, s); return;
+                case 16: z_wave4<T, 16, NC>(blocks, in, out, spec, g, tw, s); return;
+                case 32: z_wave4<T, 32, NC>(blocks, in, out, spec, g, tw, s); return;
+                case 64: z_wave4<T, 64, NC>(blocks, in, out, spec, g, tw, s); return;
+                case 128: z_wave4<T, 128, NC>(blocks, in, out, spec, g, tw, s); return;
+            }
         }
     }
     if (ev == EV) z_ev<T, EV, NC, GROUPED>(N, in, out, spec, g, tw, tk, blocks, s);
