@@ -172,6 +172,7 @@ struct ddstress_plan_s {
     bool have_density = false;
     int rows_x = 1, tk_y = 1;      // x rows and y columns per block
     int ex = 16, ey = 16, ez = 8;  // element classes of the x, y and fused z passes
+    int rows_inv = 1, ex_inv = 16; // the inverse x pass (a tuning's rows and class, or its own defaults)
     bool yx = false;               // inverse y and x as one kernel
     bool xy = false;               // forward x and y as one kernel
     double* plane_stats = nullptr; // Eq. 20 output of every stress call (device), or none
@@ -320,7 +321,7 @@ void build_spectrum(ddstress_plan_s* p, hipStream_t st) {
         gy.irs = gy.ors = s.wx;
         gy.ios = gy.oos = 0;
         gy.ips = gy.ops = (int64_t)s.P[1] * s.wx;
-        launch_col_fft<double>(s.P[1], default_ev_col(s.P[1]), true, kc.as<cplx<double>>(), kc.as<cplx<double>>(),
+        launch_col_fft<double>(s.P[1], default_ev_y(s.P[1], 8), true, kc.as<cplx<double>>(), kc.as<cplx<double>>(),
                                gy, tw, tky, st);
         ColGeom gz{};
         gz.ncols = s.M1;
@@ -331,7 +332,7 @@ void build_spectrum(ddstress_plan_s* p, hipStream_t st) {
         gz.irs = gz.ors = (int64_t)s.P[1] * s.wx;
         gz.ios = gz.oos = s.wx;
         gz.ips = gz.ops = plane_c;
-        launch_col_fft<double>(s.P[2], default_ev_col(s.P[2]), true, kc.as<cplx<double>>(), kc.as<cplx<double>>(),
+        launch_col_fft<double>(s.P[2], default_ev_y(s.P[2], 8), true, kc.as<cplx<double>>(), kc.as<cplx<double>>(),
                                gz, tw, tkz, st);
         launch_extract<T>(kc.as<cplx<double>>(), p->spec->as<T>(), l, s.C, s.M1, s.wx, s.P[1], s.P[2], s.nkys, s.nkzs,
                           s.tkz, s.ntz, s.zstrip, inv_p, maxbits.as<unsigned long long>(), st);
@@ -491,7 +492,7 @@ void enqueue_pass(ddstress_plan_s* p, int k, const T* rho, T* sigma, int nb, hip
         } else {
             if (yx) return;
             // x inverse: rows (b, v, z, y) -> Nx reals
-            launch_x_c2r<T>(s.M, p->ex, w2, sigma, B6 * Nz * Ny, Nx, s.wx, Nx, tw, p->rows_x, st, rowsq);
+            launch_x_c2r<T>(s.M, p->ex_inv, w2, sigma, B6 * Nz * Ny, Nx, s.wx, Nx, tw, p->rows_inv, st, rowsq);
             if (rowsq) launch_rowsq_finish(rowsq, B6 * Nz, Ny, inv_plane, stats_out, st);
         }
     }
@@ -611,6 +612,7 @@ bool z_ok(const Shape& s, int tk, int ev, int groups) {
 struct LaunchChoice {
     int rows_x, ex, tk_y, ey, ez, zg;
     bool yx, xy;
+    int rows_inv, ex_inv;
 };
 
 // The default fuses x and y wherever a plane fits; a tuning may ask for it by
@@ -621,8 +623,9 @@ bool yx_request_ok(const Shape& s) {
 }
 
 LaunchChoice default_launch(const Shape& s) {
-    return {default_rows(s.M, s.elem), default_ev_col(s.M), default_col_tk(s.P[1], s.elem), default_ev_col(s.P[1]),
-            default_ev_z(s.P[2], s.zg, s.elem), s.zg, yx_ok(s), yx_ok(s)};
+    const int rows = default_rows(s.M, s.elem), ex = default_ev_col(s.M), inv = default_ev_c2r(s.M);
+    return {rows, ex, default_col_tk(s.P[1], s.elem), default_ev_y(s.P[1], s.elem), default_ev_z(s.P[2], s.zg, s.elem),
+            s.zg, yx_ok(s), yx_ok(s), inv == ex ? rows : std::max(1, rows / 2), inv};
 }
 
 // Apply a tuning (zero element classes select the defaults) after checking it.
@@ -630,14 +633,15 @@ LaunchChoice apply_tuning(Shape& s, const ddstress_tuning* t) {
     LaunchChoice c = default_launch(s);
     if (!t) return c;
     const int zg = t->z_groups ? t->z_groups : c.zg;
-    const int ex = t->ex ? t->ex : c.ex, ey = t->ey ? t->ey : c.ey;
+    const int ex = t->ex ? t->ex : c.ex, ey = t->ey ? t->ey : default_ev_col(s.P[1]);
     const int ez = t->ez ? t->ez : default_ev_z(s.P[2], zg, s.elem);
     if (!rows_ok(s, t->rows_x, ex) || !col_ok(s, s.P[1], t->tk_y, ey) || !z_ok(s, t->tk_z, ez, zg))
         fail(DDSTRESS_E_INVALID, "tuning choice outside the launch limits of this shape");
     if (t->yx < 0 || t->yx > 2 || (t->yx == 2 && !yx_request_ok(s)) || t->xy < 0 || t->xy > 2 ||
         (t->xy == 2 && !yx_request_ok(s)))
         fail(DDSTRESS_E_INVALID, "fused x-y passes do not apply to this shape");
-    c = {t->rows_x, ex, t->tk_y, ey, ez, zg, t->yx == 0 ? yx_ok(s) : t->yx == 2, t->xy == 0 ? yx_ok(s) : t->xy == 2};
+    c = {t->rows_x, ex, t->tk_y, ey, ez, zg, t->yx == 0 ? yx_ok(s) : t->yx == 2, t->xy == 0 ? yx_ok(s) : t->xy == 2,
+         t->rows_x, ex};
     s.zg = zg;
     s.tkz = t->tk_z;
     s.ntz = (s.M1 + s.tkz - 1) / s.tkz;
@@ -655,6 +659,8 @@ void create_plan(const ddstress_desc* desc, const ddstress_tuning* tuning, hipSt
         const LaunchChoice lc = apply_tuning(p->shape, tuning);
         p->rows_x = lc.rows_x;
         p->ex = lc.ex;
+        p->rows_inv = lc.rows_inv;
+        p->ex_inv = lc.ex_inv;
         p->tk_y = lc.tk_y;
         p->ey = lc.ey;
         p->ez = lc.ez;
@@ -936,6 +942,8 @@ ddstress_status ddstress_plan_share(ddstress_plan src, int32_t batch, ddstress_p
             p->spec = src->spec;
             p->tw = src->tw;
             p->rows_x = src->rows_x;
+            p->rows_inv = src->rows_inv;
+            p->ex_inv = src->ex_inv;
             p->tk_y = src->tk_y;
             p->ex = src->ex;
             p->ey = src->ey;

@@ -191,6 +191,8 @@ int x_lds_ld(int M, int E, int elem_bytes);
 int col_threads(int N, int tk, int ev);
 int z_threads(int N, int groups, int tk, int ev);
 int default_ev_col(int N);
+int default_ev_y(int N, int elem_bytes);      // columns of the y passes
+int default_ev_c2r(int M);                    // inverse x pass
 int default_ev_z(int N, int groups, int elem_bytes);
 bool ev_col_ok(int ev);
 bool ev_z_ok(int N, int ev, int elem_bytes);

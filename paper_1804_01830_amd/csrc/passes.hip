@@ -250,6 +250,16 @@ bool z_stage_spec(int N, int tk, int C, int nkz, int B, int elem_bytes) {
            z_lds_bytes(N, tk, C, 1, elem_bytes) + z_stage_bytes(tk, C, nkz, elem_bytes) <= 64 * 1024;
 }
 int default_ev_col(int N) { return N <= 64 ? 8 : 16; }
+// Columns of 256 and 512 in FP64: sixteen values are 64 registers, and eight with eight
+// columns a block are faster (y forward + inverse, us: 128x128x32, one realisation
+// 44 / 50 with 16 and 16, 100x75x20, four, 91 / 103, 256x256x64 483 / 499).
+static bool narrow_col(int N, int elem_bytes) { return elem_bytes == 8 && (N == 256 || N == 512); }
+int default_ev_y(int N, int elem_bytes) { return narrow_col(N, elem_bytes) ? 8 : default_ev_col(N); }
+// The inverse x pass of class 16 runs better with eight elements and half the
+// rows (its split and its stores need the registers): us, 8 / 16 elements, 256x256x64 FP32 87 /
+// 105, periodic 44 / 47, FP64 151 / 196, 128x128x32 FP64 19.5 / 25.4; a row then
+// still lies in one wave. The forward pass prefers 16 in FP32 (85 / 93).
+int default_ev_c2r(int M) { return M >= 128 && M <= 512 ? 8 : default_ev_col(M); }
 static int base_ev_z(int elem_bytes) { return elem_bytes <= 4 ? 4 : 2; }
 constexpr int kLongZ = 256;              // shortest z length with the larger classes
 
@@ -299,6 +309,7 @@ int default_ev_z(int N, int groups, int elem_bytes) {
 bool ev_col_ok(int ev) { return ev == 8 || ev == 16; }
 
 int default_col_tk(int N, int elem_bytes) {
+    if (narrow_col(N, elem_bytes)) return 8;
     const int tc = N / ecount(N, default_ev_col(N));
     const int tk_min = elem_bytes <= 4 ? 16 : 8;
     int tk = 256 / tc;
