@@ -712,6 +712,23 @@ def measure(w, prec, Bp, args, periodic, tune, graph=False, host_io=False, stats
     return r
 
 
+def z_kernel_name(info, C, B):
+    """The kernel that a plan's fused z pass runs for B realisations of C channels."""
+    n, f32 = info.padded[2], info.precision == 32
+    if info.z_groups > 1:
+        return "k_z_grouped"
+    if f32 and n == 64 and info.ez == 8:
+        return "k_z_wave"
+    if f32 and info.ez == 4 and info.tile_z == (8 if n == 128 else 16) and (
+            (n == 16 and C > 3 and B >= 3) or (n == 32 and B >= 3) or (n == 64 and B >= (12 if C == 3 else 4)) or
+            (n == 128 and C < 9 and B >= 4)):
+        return "k_z_reg"
+    if 8 <= n <= 128 and C <= 6 and info.tile_z == 256 // n and info.ez == (4 if f32 else 2) and (
+            not f32 or (B <= 2 and (C == 3 or n <= 64))):
+        return "k_z_wave"
+    return "k_z_serial"
+
+
 def summary(r32, r64, w, C, B, periodic):
     """The fields of a bench line (or sub-object) from the FP32 and FP64 runs."""
     info = r32["info"]
@@ -719,8 +736,7 @@ def summary(r32, r64, w, C, B, periodic):
     nx, ny, nz = w["n"]
     cells = B * nx * ny * nz
     z_ms = r32["passes"]["z_fused"]
-    wave = info.z_groups == 1 and info.ez == 8 and info.padded[2] == 64 and info.precision == 32
-    kname = "k_z_grouped" if info.z_groups > 1 else ("k_z_wave" if wave else "k_z_serial")
+    kname = z_kernel_name(info, C, B)
     zmir = z_pass_bytes(info, w["n"], C, B, elem)
     from paper_1804_01830_amd import profiling as Pf
     traffic = Pf.stored_traffic(os.path.join(ROOT, "profiles"), w["name"], B, kname)
