@@ -148,6 +148,15 @@ __device__ __forceinline__ void ghost_value(const T* __restrict__ u, const T* __
 // from the real layers (Eq. 18b) while their first planes are on the way. For that
 // the last chunk marches downwards, so that a ghost plane is always a block's
 // first one (there are at least two chunks).
+//
+// STREAM: the force, read once a step, does not displace the displacements in
+// the caches.
+//
+// What bounds it: memory on large films. 256 x 256 x 64 FP32 moves 154 MB a
+// step within the 256 MB cache in 26.7 us (5.8 TB/s; with 57 LDS reads a node,
+// two barriers a layer and a ghost launch a step it was 31.1); FP64, 308 MB, 55 us
+// (66). A second plane requested ahead was no faster (27.3). Small films are bound
+// by the launch and its two memory latencies: 70 x 33 x 12 FP64 5.6 us a step (9.7).
 template <typename T, int TX, int TY, bool STREAM>
 __global__ void __launch_bounds__(TX* TY)
     k_relax_march(const T* __restrict__ u, T* __restrict__ un, const T* __restrict__ f, const T* __restrict__ phi,
