@@ -665,7 +665,7 @@ def measure(w, prec, Bp, args, periodic, tune, graph=False, host_io=False, stats
     wall, dev_ms = time_steps(plan, rho, out, steps, args.warmup)
     plan.set_density(rho, Bd.DEVICE_BORROW)
     passes = plan.time_passes(out, max(20, min(steps, 100)))
-    r = dict(info=plan.info(), steps=steps, ms_per_step=wall / steps * 1e3, device_ms_per_step=dev_ms / steps,
+    r = dict(info=plan.info(), z_form=plan.z_form(), steps=steps, ms_per_step=wall / steps * 1e3, device_ms_per_step=dev_ms / steps,
              lat=lat, passes=passes, plan_s=plan_s, nye_ms=nye_ms, cells=Bp * nx * ny * nz,
              tune=Tn.to_dict(tuning) if tuning is not None else None)
     r["value"] = r["cells"] / (r["ms_per_step"] * 1e-3)
@@ -712,23 +712,6 @@ def measure(w, prec, Bp, args, periodic, tune, graph=False, host_io=False, stats
     return r
 
 
-def z_kernel_name(info, C, B):
-    """The kernel that a plan's fused z pass runs for B realisations of C channels."""
-    n, f32 = info.padded[2], info.precision == 32
-    if info.z_groups > 1:
-        return "k_z_grouped"
-    if f32 and n == 64 and info.ez == 8:
-        return "k_z_wave"
-    if f32 and info.ez == 4 and info.tile_z == (8 if n == 128 else 16) and (
-            (n == 16 and C > 3 and B >= 3) or (n == 32 and B >= 3) or (n == 64 and B >= (12 if C == 3 else 4)) or
-            (n == 128 and C < 9 and B >= 4)):
-        return "k_z_reg"
-    if 8 <= n <= 128 and C <= 6 and info.tile_z == 256 // n and info.ez == (4 if f32 else 2) and (
-            not f32 or (B <= 2 and (C == 3 or n <= 64))):
-        return "k_z_wave"
-    return "k_z_serial"
-
-
 def summary(r32, r64, w, C, B, periodic):
     """The fields of a bench line (or sub-object) from the FP32 and FP64 runs."""
     info = r32["info"]
@@ -736,7 +719,7 @@ def summary(r32, r64, w, C, B, periodic):
     nx, ny, nz = w["n"]
     cells = B * nx * ny * nz
     z_ms = r32["passes"]["z_fused"]
-    kname = z_kernel_name(info, C, B)
+    kname, _, z_threads, z_blocks = r32["z_form"]
     zmir = z_pass_bytes(info, w["n"], C, B, elem)
     from paper_1804_01830_amd import profiling as Pf
     traffic = Pf.stored_traffic(os.path.join(ROOT, "profiles"), w["name"], B, kname)
@@ -777,7 +760,8 @@ def summary(r32, r64, w, C, B, periodic):
         "plan_build_s": {"fp32": round(r32["plan_s"], 3), "fp64": round(r64["plan_s"], 3)},
         "roofline": roofline,
         "plan_info": {"padded": list(info.padded), "tile_z": info.tile_z, "ez": info.ez,
-                      "z_groups": info.z_groups, "mirror_y": info.mirror_y, "mirror_z": info.mirror_z,
+                      "z_groups": info.z_groups, "z_threads": z_threads, "z_blocks": z_blocks,
+                      "mirror_y": info.mirror_y, "mirror_z": info.mirror_z,
                       "xy_fused": info.xy_fused, "yx_fused": info.yx_fused,
                       "rows_x": info.rows_x, "tile_y": info.tile_y, "ex": info.ex, "ey": info.ey},
     }

@@ -259,6 +259,23 @@ ddstress_status ddstress_stress_batch(ddstress_plan plan, const void* rho, void*
 /* Facts about a plan (see ddstress_info). */
 ddstress_status ddstress_plan_get_info(ddstress_plan plan, ddstress_info* info);
 
+/* The launch of the fused z pass in a call on `nbatch` realisations (1 <=
+ * nbatch <= batch): which of its kernels runs, the kx columns, threads and number
+ * of its blocks. The choice changes the speed, not the result. */
+enum {
+    DDSTRESS_Z_SERIAL = 0,   /* one thread group, accumulators in registers */
+    DDSTRESS_Z_GROUPED = 1,  /* one thread group per channel (z_groups = C) */
+    DDSTRESS_Z_WAVE = 2,     /* one wave per realisation, channel spectra in registers */
+    DDSTRESS_Z_REGISTER = 3  /* one wave per realisation, whole columns in registers */
+};
+typedef struct {
+    int32_t form;            /* DDSTRESS_Z_* */
+    int32_t tile;            /* kx columns per block */
+    int32_t threads;         /* threads per block */
+    int64_t blocks;
+} ddstress_z_launch;
+ddstress_status ddstress_plan_z_form(ddstress_plan plan, int32_t nbatch, ddstress_z_launch* out);
+
 /* Per-pass timing with HIP events recorded on the stream of each stress()
  * call: enable != 0 switches it on (and clears the totals), 0 switches it off.
  * The five passes are, in order: x real-to-complex, y forward, fused z

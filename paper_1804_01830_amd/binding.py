@@ -19,7 +19,7 @@ STATUS_NAMES = {0: "OK", 1: "E_INVALID", 2: "E_NOMEM", 3: "E_DEVICE", 4: "E_STAT
 # names exported by the library, in header order
 EXPORTS = ("ddstress_plan_footprint", "ddstress_autotune", "ddstress_plan_create", "ddstress_plan_create_tuned",
            "ddstress_set_density", "ddstress_stress",
-           "ddstress_plan_share", "ddstress_stress_batch", "ddstress_plan_get_info", "ddstress_plan_set_profiling", "ddstress_plan_set_graph", "ddstress_plan_get_pass_times", "ddstress_plan_time_passes",
+           "ddstress_plan_share", "ddstress_stress_batch", "ddstress_plan_get_info", "ddstress_plan_z_form", "ddstress_plan_set_profiling", "ddstress_plan_set_graph", "ddstress_plan_get_pass_times", "ddstress_plan_time_passes",
            "ddstress_plan_destroy", "ddstress_kernel_realspace", "ddstress_plan_set_plane_stats", "ddstress_stress_batch_stats_noalloc",
            "ddstress_nye_density",
            "ddstress_plane_mean_square",
@@ -52,6 +52,14 @@ class Info(ctypes.Structure):
                 ("mirror_z", ctypes.c_int32),
                 ("cached_bytes", ctypes.c_size_t), ("work_bytes", ctypes.c_size_t),
                 ("kernel_real_max", ctypes.c_double), ("kernel_imag_max", ctypes.c_double)]
+
+
+class ZLaunch(ctypes.Structure):
+    _fields_ = [("form", ctypes.c_int32), ("tile", ctypes.c_int32), ("threads", ctypes.c_int32),
+                ("blocks", ctypes.c_int64)]
+
+
+Z_KERNELS = ("k_z_serial", "k_z_grouped", "k_z_wave", "k_z_reg")     # by ZLaunch.form
 
 
 class RelaxDesc(ctypes.Structure):
@@ -91,6 +99,8 @@ def load(path=LIB_PATH):
     lib.ddstress_set_density.argtypes = [P, P, ctypes.c_int32, P]
     lib.ddstress_stress.argtypes = [P, P, ctypes.c_int32, P]
     lib.ddstress_plan_get_info.argtypes = [P, ctypes.POINTER(Info)]
+    lib.ddstress_plan_z_form.argtypes = [P, ctypes.c_int32, ctypes.POINTER(ZLaunch)]
+    lib.ddstress_plan_z_form.restype = ctypes.c_int
     lib.ddstress_plan_destroy.argtypes = [P]
     lib.ddstress_kernel_realspace.argtypes = [ctypes.POINTER(Desc), ctypes.c_int32, P, P]
     lib.ddstress_plan_set_profiling.argtypes = [P, ctypes.c_int32]
@@ -198,6 +208,13 @@ class Plan:
         info = Info()
         check(load().ddstress_plan_get_info(self._h, ctypes.byref(info)))
         return info
+
+    def z_form(self, nbatch=None):
+        """The fused z launch of a call on ``nbatch`` realisations (default:
+        the plan's batch): (kernel name, kx columns, threads, blocks)."""
+        l = ZLaunch()
+        check(load().ddstress_plan_z_form(self._h, int(self.batch if nbatch is None else nbatch), ctypes.byref(l)))
+        return Z_KERNELS[l.form], l.tile, l.threads, l.blocks
 
     @property
     def handle(self):

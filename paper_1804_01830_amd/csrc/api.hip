@@ -1033,6 +1033,17 @@ ddstress_status ddstress_plan_get_info(ddstress_plan plan, ddstress_info* info) 
     });
 }
 
+ddstress_status ddstress_plan_z_form(ddstress_plan plan, int32_t nbatch, ddstress_z_launch* out) {
+    return guarded([&] {
+        if (!plan || !out) fail(DDSTRESS_E_INVALID, "NULL argument");
+        if (nbatch < 1 || nbatch > plan->shape.B) fail(DDSTRESS_E_INVALID, "nbatch must lie in [1, batch]");
+        const Shape& s = plan->shape;
+        ZGeom g = z_geom(s, s.tkz, nbatch, plan->xy, plan->yx);
+        const ZLaunch l = z_launch_plan(s.P[2], plan->ez, s.zg, g, s.tkz, s.elem);
+        *out = {l.form, s.tkz, l.threads, l.blocks};
+    });
+}
+
 ddstress_status ddstress_plan_set_profiling(ddstress_plan plan, int32_t enable) {
     return guarded([&] {
         if (!plan) fail(DDSTRESS_E_INVALID, "plan is NULL");

@@ -160,6 +160,13 @@ struct ZGeom {
     int strip;             // the spectrum keeps the Nyquist strip where the tiles allow it
     int nyq;               // groups of the Nyquist strip (z_nyq_groups; set by launch_z_fused)
     int sb;                // realisations per block of the strip (set by launch_z_fused)
+    int form;              // ZForm of the launch (set by launch_z_fused)
+};
+// The kernels of the fused z pass (values of ddstress_z_launch.form).
+enum ZForm { kZSerial = 0, kZGrouped = 1, kZWave = 2, kZReg = 3 };
+struct ZLaunch {
+    int form, threads;     // kernel and threads per block
+    int64_t blocks;
 };
 // Plans of at least this many realisations keep the Nyquist strip.
 constexpr int kZStripBatch = 4;
@@ -180,6 +187,8 @@ __host__ __device__ inline int z_nyq_groups(int ncols, int tk, int nky) {
 template <typename T>
 void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& g,
                     const cplx<T>* tw, int tk, hipStream_t s);
+// The launch that it makes; sets g's fields that are marked so.
+ZLaunch z_launch_plan(int N, int ev, int groups, ZGeom& g, int tk, int elem_bytes);
 
 // Launch geometry: threads per block, element classes and defaults.
 int x_threads(int M, int rows, int ev);
@@ -220,6 +229,7 @@ size_t z_wave_lds_bytes(int N, int C, int nkz, int B);
 bool z_reg_applies(int N, int C, int B);
 int z_reg_tile(int N);
 int z_reg_waves(int B);                  // waves per block
+int z_reg_split(int N, int C);           // blocks per tile
 size_t z_reg_lds_bytes(int N, int C, int nkz);
 void z_reg_dispatch(int N, int C, const cplx<float>* in, cplx<float>* out, const float* spec, const ZGeom& g,
                     const cplx<float>* tw, int64_t blocks, hipStream_t s);

@@ -574,20 +574,44 @@ void launch_col_fft(int N, int ev, bool forward, const cplx<T>* in, cplx<T>* out
     check_hip(hipGetLastError(), "column fft launch");
 }
 
+// The kernel of a fused z launch: the form that its tile width, batch and
+// element class select (the register form takes over wherever its tile and
+// enough realisations are given), and its grid: tiles x ky rows; in place of the
+// Nyquist strip's tile, its groups x realisations.
+ZLaunch z_launch_plan(int N, int ev, int groups, ZGeom& g, int tk, int elem_bytes) {
+    ZLaunch l{kZSerial, z_threads(N, groups, tk, ev), 0};
+    const bool wave8 = z_wave_form(N, ev, groups, elem_bytes);
+    g.nyq = g.strip ? z_nyq_groups(g.ncols, tk, g.nky) : 0;
+    g.sb = 1;
+    if (groups != 1) {
+        l.form = kZGrouped;
+    } else if (elem_bytes == 4 && ev == 4 && z_reg_applies(N, g.C, g.B) && tk == z_reg_tile(N)) {
+        l.form = kZReg;
+        g.sb = z_reg_waves(g.B);
+        l.threads = 64 * g.sb;
+    } else if (wave8) {
+        l.form = kZWave;
+        l.threads = 64 * z_wave4_waves(g.B);
+    } else if (z_wave4_applies(N, g.C, g.B, ev, tk, elem_bytes)) {
+        l.form = kZWave;
+        g.sb = z_wave4_waves(g.B);
+        l.threads = 64 * g.sb;
+    }
+    g.form = l.form;
+    l.blocks = g.nyq > 0 ? (int64_t)(g.ntiles - 1) * g.nky + (int64_t)g.nyq * ((g.B + g.sb - 1) / g.sb)
+                         : (int64_t)g.ntiles * g.nky;
+    if (l.form == kZReg) l.blocks *= z_reg_split(N, g.C);
+    return l;
+}
+
 template <typename T>
 void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& geom,
                     const cplx<T>* tw, int tk, hipStream_t s) {
     if (tk < 1 || geom.ntiles != (geom.ncols + tk - 1) / tk)
         fail(DDSTRESS_E_INVALID, "fused z tiles do not match the tile width");
     ZGeom g = geom;
-    g.nyq = g.strip ? z_nyq_groups(g.ncols, tk, g.nky) : 0;
-    // tiles x ky rows; in place of the Nyquist strip's tile, its groups x realisations
-    // the register form takes over wherever its tile and enough realisations are given
-    const bool reg = sizeof(T) == 4 && groups == 1 && ev == 4 && z_reg_applies(N, g.C, g.B) && tk == z_reg_tile(N);
-    const bool wave4 = groups == 1 && !reg && z_wave4_applies(N, g.C, g.B, ev, tk, (int)sizeof(T));
-    g.sb = reg ? z_reg_waves(g.B) : wave4 ? z_wave4_waves(g.B) : 1;
-    const int64_t blocks = g.nyq > 0 ? (int64_t)(g.ntiles - 1) * g.nky + (int64_t)g.nyq * ((g.B + g.sb - 1) / g.sb)
-                                     : (int64_t)g.ntiles * g.nky;
+    const ZLaunch l = z_launch_plan(N, ev, groups, g, tk, (int)sizeof(T));
+    const int64_t blocks = l.blocks;
     if (blocks <= 0) return;
     if (blocks > 0x7fffffffLL) fail(DDSTRESS_E_UNSUPPORTED, "grid too large for one launch");
     if (!ev_z_ok(N, ev, (int)sizeof(T))) fail(DDSTRESS_E_INVALID, "z element class not supported for this length");
@@ -601,7 +625,7 @@ void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, 
         fail(DDSTRESS_E_INVALID, "fused z block exceeds the thread or LDS limit");
     }
     if constexpr (sizeof(T) == 4) {
-        if (reg) {
+        if (l.form == kZReg) {
             z_reg_dispatch(N, g.C, in, out, spec, g, tw, blocks, s);
             check_hip(hipGetLastError(), "fused z launch");
             return;

@@ -30,6 +30,11 @@ int z_reg_waves(int B) {
     return (B + rounds - 1) / rounds;
 }
 
+int z_reg_split(int N, int C) {
+    const int vg = z_reg_vg(N, C);
+    return vg > 0 ? 6 / vg : 1;
+}
+
 // The staged spectrum tile, and for eight lanes per column the twiddle table
 // of both directions.
 size_t z_reg_lds_bytes(int N, int C, int nkz) {

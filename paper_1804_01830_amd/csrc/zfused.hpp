@@ -832,7 +832,7 @@ void z_dispatch(int N, int ev, const cplx<T>* in, cplx<T>* out, const T* spec, c
         }
     }
     if constexpr (!GROUPED && NC <= 6) {
-        if (z_wave4_applies(N, NC, g.B, ev, tk, (int)sizeof(T))) {
+        if (g.form == kZWave) {
             switch (N) {
                 case 8: z_wave4<T, 8, NC>(blocks, in, out, spec, g, tw, s); return;
                 case 16: z_wave4<T, 16, NC>(blocks, in, out, spec, g, tw, s); return;

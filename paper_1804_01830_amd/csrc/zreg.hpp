@@ -412,7 +412,6 @@ void z_reg_launch(int64_t blocks, const cplx<float>* in, cplx<float>* out, const
     constexpr int LP = z_reg_lanes(N);
     constexpr int VG = z_reg_vg(N, NC);
     const size_t lds = z_reg_lds_bytes(N, NC, g.nkz_s);
-    blocks *= VG > 0 ? 6 / VG : 1;
     if (lds > (size_t)80 * 1024 || blocks > 0x7fffffffLL)
         fail(DDSTRESS_E_UNSUPPORTED, "fused z register form: grid or spectrum tile too large");
     const dim3 grid((unsigned)blocks), block(64 * z_reg_waves(g.B));

@@ -75,9 +75,9 @@ def trace_report(directory, title, command):
 
 def _z_shape(line):
     """Block size and grid (threads) of the benchmarked plan's fused z launches."""
-    cfg, tune = line["config"], line.get("tuning") or {}
-    nx, ny, nz = cfg["grid"]
-    info = line["plan_info"]
+    cfg, info = line["config"], line["plan_info"]
+    if "z_threads" in info:                       # as the library launches it
+        return info["z_threads"], info["z_blocks"] * info["z_threads"]
     pz = info["padded"][2]
     groups = info["z_groups"]
     tk = info["tile_z"]
@@ -102,7 +102,7 @@ def traffic(fetch_dir, write_dir, line, copy_mib):
     for counter, directory in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = [r for r in _csv(directory, "counter_collection.csv") if r["Counter_Name"] == counter]
         z = [float(r["Counter_Value"]) for r in rows
-             if re.search(r"k_z_(serial|grouped|wave)<", r["Kernel_Name"])
+             if re.search(r"k_z_(serial|grouped|wave|reg)<", r["Kernel_Name"])
              and int(r["Workgroup_Size"]) == block and int(r["Grid_Size"]) == grid]
         other = [float(r["Counter_Value"]) for r in rows if "dds::" not in r["Kernel_Name"]]
         if not z or not other:
