@@ -760,8 +760,10 @@ static void z_launch(int64_t blocks, int tk, const cplx<T>* in, cplx<T>* out, co
             const dim3 grid((unsigned)blocks);
             const auto staged = [&](auto tkc) {
                 constexpr int TK = decltype(tkc)::value;
-                if constexpr (!(sizeof(T) == 8 && E == 2 && L >= 8 && L <= 128 && TK * L == 256))   // (the wave form)
+                if constexpr (!(sizeof(T) == 8 && E == 2 && L >= 8 && L <= 128 && TK * L == 256))
                     hipLaunchKernelGGL((k_z_serial<T, L, E, NC, TK>), grid, block, lds, s, in, out, spec, g, tw, tk, ld);
+                else    // (the wave form's shapes: no instance)
+                    fail(DDSTRESS_E_INVALID, "fused z pass: this tile runs in the wave form only");
             };
             if (tk == 4) staged(std::integral_constant<int, 4>{});
             else if (tk == 8) staged(std::integral_constant<int, 8>{});
