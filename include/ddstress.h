@@ -126,7 +126,9 @@ typedef struct {
     int32_t channels;      /* C = 3 L */
     int32_t batch;         /* B */
     int32_t precision;     /* 32 or 64 */
-    int32_t tile_z;        /* columns per block of the fused z kernel (fixes the spectrum layout) */
+    int32_t tile_z;        /* kx columns of a tile of the stored spectrum: those of a block of the fused z
+                              kernel, but in calls of more realisations than the spectrum was built for
+                              (ddstress_plan_z_form) */
     int32_t tile_y;        /* columns per block of the y passes */
     int32_t rows_x;        /* rows per block of the x passes */
     int32_t ex, ey, ez;    /* element classes of the x, y and fused z passes (see ddstress_tuning) */
@@ -244,7 +246,9 @@ ddstress_status ddstress_stress(ddstress_plan plan, void* sigma, int32_t where, 
  * precision, near shells) for `batch` realisations, with its own work buffers
  * and the kernel spectrum of `src` shared, not copied: the spectrum stays
  * alive until the last plan sharing it is destroyed. No device work; plans
- * sharing a spectrum may run concurrently on distinct streams. */
+ * sharing a spectrum may run concurrently on distinct streams. A call runs the
+ * z kernel of its own number of realisations, whatever batch the spectrum was
+ * built for (a tuned plan's sharers keep its launch shapes). */
 ddstress_status ddstress_plan_share(ddstress_plan src, int32_t batch, ddstress_plan* out);
 
 /* One-shot evaluation of the first `nbatch` (1 <= nbatch <= batch) densities:

@@ -173,6 +173,7 @@ struct ddstress_plan_s {
     int rows_x = 1, tk_y = 1;      // x rows and y columns per block
     int ex = 16, ey = 16, ez = 8;  // element classes of the x, y and fused z passes
     int rows_inv = 1, ex_inv = 16; // the inverse x pass (a tuning's rows and class, or its own defaults)
+    bool tuned = false;            // launch shapes given by the caller
     bool yx = false;               // inverse y and x as one kernel
     bool xy = false;               // forward x and y as one kernel
     double* plane_stats = nullptr; // Eq. 20 output of every stress call (device), or none
@@ -419,8 +420,9 @@ ColGeom inv_y_geom(const Shape& s, int64_t groups) {
     g.ops = (int64_t)Ny * s.wx;
     return g;
 }
-// Fused z pass: the density buffer ky-major when kin, the stress buffer when kout.
-ZGeom z_geom(const Shape& s, int tk, int nb, bool kin, bool kout) {
+// Fused z pass in tiles of tk columns on a spectrum stored in tiles of stk: the
+// density buffer ky-major when kin, the stress buffer when kout.
+ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
     const int Nz = s.N[2], Py = s.P[1];
     ZGeom g{};
     g.nky_s = s.nkys;
@@ -440,7 +442,30 @@ ZGeom z_geom(const Shape& s, int tk, int nb, bool kin, bool kout) {
     g.oos = kout ? (int64_t)Nz * s.wx : s.wx;
     g.oqs = g.iqs;
     g.strip = s.zstrip ? 1 : 0;
+    g.stk = stk;
+    g.snt = (s.M1 + stk - 1) / stk;
     return g;
+}
+
+// Columns per block of the fused z pass in a call on nb realisations. The
+// spectrum's tile is the default of the batch that it was built for; a plan that
+// shares it for more realisations runs the kernel and the tile of those (or the
+// widest narrower one that can), whose blocks then copy several spectrum tiles each. A
+// tuned plan keeps its tile, and so do the forms that read the spectrum in place.
+// us, whole FP32 calls of eight realisations on the spectrum of a plan of one,
+// this tile / the spectrum's own (a plan of eight): three channels 128x128x32 437 / 478 (418),
+// 256x256x32 2046 / 2372 (1999), 128x128x64 865 / 1133 (847); six 592 / 774 (568), 2871 / 3557 (2789), 1232 /
+// 1527 (1198); nine 811 / 1067 (785), 3926 / 4962 (3846). In-place reads of narrower tiles by the unstaged
+// kernel were tried: its scalar registers are short, and one stride more cost it 10 to 20 percent.
+int z_call_tile(const ddstress_plan_s* p, int nb) {
+    const Shape& s = p->shape;
+    if (p->tuned || s.zg != 1) return s.tkz;
+    for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem); tk > s.tkz; tk /= 2) {
+        ZGeom g = z_geom(s, tk, s.tkz, nb, false, false);
+        z_launch_plan(s.P[2], p->ez, 1, g, tk, s.elem);
+        if (z_retile_ok(s.P[2], g, tk, s.elem)) return tk;
+    }
+    return s.tkz;
 }
 
 struct StatsTarget {
@@ -474,7 +499,8 @@ void enqueue_pass(ddstress_plan_s* p, int k, const T* rho, T* sigma, int nb, hip
         launch_col_fft<T>(Py, p->ey, true, w1, w2, fwd_y_geom(s, BC), tw, p->tk_y, st);
     } else if (k == 2) {
         // z forward + contraction + z inverse
-        launch_z_fused<T>(s.P[2], p->ez, s.zg, w2, w1, p->spec->as<T>(), z_geom(s, s.tkz, s.B, xy, yx), tw, s.tkz,
+        const int tk = z_call_tile(p, nb);
+        launch_z_fused<T>(s.P[2], p->ez, s.zg, w2, w1, p->spec->as<T>(), z_geom(s, tk, s.tkz, nb, xy, yx), tw, tk,
                           st);
     } else if (k == 3 || k == 4) {
         // plane statistics (Eq. 20) from per-row sums of the inverse x pass
@@ -664,6 +690,7 @@ void create_plan(const ddstress_desc* desc, const ddstress_tuning* tuning, hipSt
         p->tk_y = lc.tk_y;
         p->ey = lc.ey;
         p->ez = lc.ez;
+        p->tuned = tuning != nullptr;
         p->yx = lc.yx;
         p->xy = lc.xy;
         const Shape& s = p->shape;
@@ -786,7 +813,7 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
     for (auto& z : zlist) {
         const int tk = z.tk, ev = z.ev, groups = z.groups;
         // the layouts of fused x-y passes where they apply (they are chosen below)
-        ZGeom gz = z_geom(s, tk, s.B, yx_ok(s), yx_ok(s));
+        ZGeom gz = z_geom(s, tk, tk, s.B, yx_ok(s), yx_ok(s));
         gz.sgn_y = gz.sgn_z = 0;                 // (the tuning spectrum is zeros)
         float ms = time_median(st, reps, [&] {
             launch_z_fused<T>(Pz, ev, groups, w2.as<cplx<T>>(), w1.as<cplx<T>>(), spec.as<T>(), gz, twp, tk, st);
@@ -948,6 +975,7 @@ ddstress_status ddstress_plan_share(ddstress_plan src, int32_t batch, ddstress_p
             p->ex = src->ex;
             p->ey = src->ey;
             p->ez = src->ez;
+            p->tuned = src->tuned;
             p->yx = src->yx;
             p->xy = src->xy;
             p->re_max = src->re_max;
@@ -1038,9 +1066,10 @@ ddstress_status ddstress_plan_z_form(ddstress_plan plan, int32_t nbatch, ddstres
         if (!plan || !out) fail(DDSTRESS_E_INVALID, "NULL argument");
         if (nbatch < 1 || nbatch > plan->shape.B) fail(DDSTRESS_E_INVALID, "nbatch must lie in [1, batch]");
         const Shape& s = plan->shape;
-        ZGeom g = z_geom(s, s.tkz, nbatch, plan->xy, plan->yx);
-        const ZLaunch l = z_launch_plan(s.P[2], plan->ez, s.zg, g, s.tkz, s.elem);
-        *out = {l.form, s.tkz, l.threads, l.blocks};
+        const int tk = z_call_tile(plan, nbatch);
+        ZGeom g = z_geom(s, tk, s.tkz, nbatch, plan->xy, plan->yx);
+        const ZLaunch l = z_launch_plan(s.P[2], plan->ez, s.zg, g, tk, s.elem);
+        *out = {l.form, tk, l.threads, l.blocks};
     });
 }
 

@@ -158,7 +158,9 @@ struct ZGeom {
     int64_t irs, iqs, ios; // input z / plane / ky strides
     int64_t ors, oqs, oos; // output strides (6B planes)
     int strip;             // the spectrum keeps the Nyquist strip where the tiles allow it
-    int nyq;               // groups of the Nyquist strip (z_nyq_groups; set by launch_z_fused)
+    int stk, snt;          // columns of a spectrum tile, and tiles per stored ky row
+    int sratio, sts;       // spectrum tiles per block, and log2 stk (1 and 31 where the two widths are the same)
+    int nyq, snyq;         // groups of the Nyquist strip, of tk and of stk rows (z_nyq_groups; set by launch_z_fused)
     int sb;                // realisations per block of the strip (set by launch_z_fused)
     int form;              // ZForm of the launch (set by launch_z_fused)
 };
@@ -187,6 +189,11 @@ __host__ __device__ inline int z_nyq_groups(int ncols, int tk, int nky) {
 template <typename T>
 void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& g,
                     const cplx<T>* tw, int tk, hipStream_t s);
+// Whether the launch of z_launch_plan can read a spectrum whose tiles (g.stk) are
+// narrower than its blocks: by the forms that stage the spectrum for base-class
+// transforms, whole tiles a block, in pairs of values or wider, the Nyquist strip
+// kept by both widths or none.
+bool z_retile_ok(int N, const ZGeom& g, int tk, int elem_bytes);
 // The launch that it makes; sets g's fields that are marked so.
 ZLaunch z_launch_plan(int N, int ev, int groups, ZGeom& g, int tk, int elem_bytes);
 

@@ -582,6 +582,7 @@ ZLaunch z_launch_plan(int N, int ev, int groups, ZGeom& g, int tk, int elem_byte
     ZLaunch l{kZSerial, z_threads(N, groups, tk, ev), 0};
     const bool wave8 = z_wave_form(N, ev, groups, elem_bytes);
     g.nyq = g.strip ? z_nyq_groups(g.ncols, tk, g.nky) : 0;
+    g.snyq = g.strip ? z_nyq_groups(g.ncols, g.stk, g.nky) : 0;
     g.sb = 1;
     if (groups != 1) {
         l.form = kZGrouped;
@@ -598,19 +599,32 @@ ZLaunch z_launch_plan(int N, int ev, int groups, ZGeom& g, int tk, int elem_byte
         l.threads = 64 * g.sb;
     }
     g.form = l.form;
+    g.sratio = tk == g.stk ? 1 : tk / g.stk;
+    g.sts = 31;
+    if (tk != g.stk) for (g.sts = 0; (1 << g.sts) < g.stk;) ++g.sts;
     l.blocks = g.nyq > 0 ? (int64_t)(g.ntiles - 1) * g.nky + (int64_t)g.nyq * ((g.B + g.sb - 1) / g.sb)
                          : (int64_t)g.ntiles * g.nky;
     if (l.form == kZReg) l.blocks *= z_reg_split(N, g.C);
     return l;
 }
 
+bool z_retile_ok(int N, const ZGeom& g, int tk, int elem_bytes) {
+    const bool pow2 = (tk & (tk - 1)) == 0 && (g.stk & (g.stk - 1)) == 0;
+    return pow2 && tk > g.stk && g.stk * elem_bytes >= 8 &&
+           (g.form == kZReg || (g.form == kZSerial && z_stage_spec(N, tk, g.C, g.nkz_s, g.B, elem_bytes))) &&
+           (g.nyq > 0) == (g.snyq > 0);
+}
+
 template <typename T>
 void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& geom,
                     const cplx<T>* tw, int tk, hipStream_t s) {
-    if (tk < 1 || geom.ntiles != (geom.ncols + tk - 1) / tk)
+    if (tk < 1 || geom.ntiles != (geom.ncols + tk - 1) / tk || geom.stk < 1 ||
+        geom.snt != (geom.ncols + geom.stk - 1) / geom.stk)
         fail(DDSTRESS_E_INVALID, "fused z tiles do not match the tile width");
     ZGeom g = geom;
     const ZLaunch l = z_launch_plan(N, ev, groups, g, tk, (int)sizeof(T));
+    if (tk != g.stk && !z_retile_ok(N, g, tk, (int)sizeof(T)))
+        fail(DDSTRESS_E_INVALID, "fused z tile does not fit the spectrum's");
     const int64_t blocks = l.blocks;
     if (blocks <= 0) return;
     if (blocks > 0x7fffffffLL) fail(DDSTRESS_E_UNSUPPORTED, "grid too large for one launch");

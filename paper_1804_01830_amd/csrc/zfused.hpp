@@ -48,8 +48,14 @@ __device__ __forceinline__ NyquistRole nyquist_role(int tile, int tk, int col, i
     return {tile * tk == m && upper, valid && !(nyq && upper), nyq && ky > 0 && 2 * ky < g.nky};
 }
 
+// Offset of column c of a block's tile from the block's first spectrum value, with
+// `part` values from one of its spectrum tiles to the next.
+__device__ __forceinline__ int spec_col(const ZGeom& g, int part, int c) {
+    return (c >> g.sts) * part + (c & (int)((1u << g.sts) - 1u));
+}
+
 // Roles of a block of the fused z pass and of its lane in column slot c of
-// the tile: the spectrum tile and stored row it reads, the element offsets of
+// the tile: the spectrum tiles it reads (one, or several narrower ones), the element offsets of
 // its input and output columns, and its realisations [b0, b1). With a Nyquist
 // strip (g.nyq groups, see z_nyq_groups) the last tile is the strip, whose
 // blocks hold the column kx = M at ky = q tk + c for group q. A strip lane
@@ -68,7 +74,8 @@ __device__ __forceinline__ int z_logical_block(const ZGeom& g, int split = 1) {
     return b < strip ? b : strip + xcd_block(b - strip, (int)gridDim.x - strip);
 }
 struct ZRoles {
-    int tile, kyc;        // spectrum tile and stored row
+    int tile, kyc;        // spectrum tile (the first of g.sratio) and stored row
+    int parts, stride;    // spectrum tiles of the block that there are, and tiles from one to the next
     bool flip_y;          // row kyc is the y mirror of the block's ky (odd planes change sign)
     int64_t in0;          // offset of the block's first input column in a density plane
     int lane_in;          // offset of this lane's column from in0 (lanes without data: 0, a valid column)
@@ -93,9 +100,11 @@ __device__ __forceinline__ ZRoles z_roles(int blk, int tk, int c, const ZGeom& g
         const int ky = q * tk + c;
         const bool valid = 2 * ky <= g.nky;
         const int kyv = valid ? ky : q * tk;
-        r.tile = g.ntiles - 1;
-        r.kyc = q;
         r.flip_y = false;
+        r.tile = g.snt - 1;
+        r.kyc = q * g.sratio;
+        r.parts = min(g.sratio, g.snyq - r.kyc);
+        r.stride = g.snt;                        // (the strip's tiles are one to a stored row)
         r.in0 = (int64_t)q * tk * g.ios + m;
         r.lane_in = valid ? c * (int)g.ios : 0;
         r.own = (int64_t)kyv * g.oos + m;
@@ -114,9 +123,11 @@ __device__ __forceinline__ ZRoles z_roles(int blk, int tk, int c, const ZGeom& g
     const int colc = valid ? col : 0;
     r.b0 = 0;
     r.b1 = g.B;
-    r.tile = tile;
     r.flip_y = g.nky_s < g.nky && 2 * ky > g.nky;
     r.kyc = r.flip_y ? g.nky - ky : ky;
+    r.tile = tile * g.sratio;
+    r.parts = min(g.sratio, g.snt - r.tile);
+    r.stride = 1;
     r.in0 = (int64_t)ky * g.ios + (int64_t)tile * tk;
     r.lane_in = valid ? c : 0;
     r.own = (int64_t)ky * g.oos + colc;
@@ -150,15 +161,35 @@ __device__ __forceinline__ double flip_sign(double x, uint32_t msk) {
 }
 __device__ __forceinline__ uint32_t sign_mask(bool neg) { return neg ? 0x80000000u : 0u; }
 
+// Values from one of a block's spectrum tiles to the next, and the resource that
+// covers them from the first value sp on (its length by way of a scalar register: as the
+// result of vector arithmetic it would cost a loop at every access).
+__device__ __forceinline__ int split_part(const ZRoles& ro, const ZGeom& g) {
+    return ro.stride * g.C * 6 * g.nkz_s * g.stk;
+}
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t split_rsrc(const T* sp, const ZRoles& ro, const ZGeom& g) {
+    const int values = (ro.parts - 1) * split_part(ro, g) + g.C * 6 * g.nkz_s * g.stk;
+    return make_rsrc(sp, (uint32_t)__builtin_amdgcn_readfirstlane(values) * (uint32_t)sizeof(T));
+}
+// Half a piece of a staged tile (8 bytes at a byte offset; kNoOffset, beyond every
+// resource, reads zero).
+constexpr int kNoOffset = 0x7ffffff0;
+__device__ __forceinline__ uint2 spec_half(__amdgpu_buffer_rsrc_t srs, int off) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(srs, off, 0, 0));
+}
+
 // Copy a block's spectrum tile [c][v][kz][TK] (nkz rows kz, NC channels,
 // six components) into LDS as rows kz of [c][v][TK] values with the row
 // stride (6 NC + 1) TK, applying the y-mirror sign of the odd planes (bit
 // c 6 + v of sgn_y) when flip_y. NT threads (tid < NT) copy 16-byte pieces,
 // up to CH loads each in flight before their stores; a piece never straddles
-// a source row (TK is a multiple of its width). The caller synchronises.
-template <typename T, int NC, int TK, int NT, int CH = 16>
+// a source row (TK is a multiple of its width). SPLIT: the spectrum's tiles are
+// narrower than the block's, and a piece is read in two halves. The caller
+// synchronises.
+template <typename T, int NC, int TK, int NT, bool SPLIT = false, int CH = 16>
 __device__ __forceinline__ void stage_spectrum_tile(T* s_l, __amdgpu_buffer_rsrc_t srs, int nkz, bool flip_y,
-                                                    uint64_t sgn_y, int tid) {
+                                                    uint64_t sgn_y, int tid, const ZGeom* g = nullptr, int part = 0) {
     constexpr int KS = (6 * NC + 1) * TK;
     constexpr int VW = 16 / (int)sizeof(T);
     const int n_vals = NC * 6 * nkz * TK;
@@ -166,9 +197,18 @@ __device__ __forceinline__ void stage_spectrum_tile(T* s_l, __amdgpu_buffer_rsrc
     for (int k0 = 0; k0 * NT * VW < n_vals; k0 += CH) {
         uint4 piece[CH];
 #pragma unroll
-        for (int k = 0; k < CH; ++k)
-            piece[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(srs, (tid + (k0 + k) * NT) * 16,
-                                                                                    0, 0));
+        for (int k = 0; k < CH; ++k) {
+            if constexpr (SPLIT) {
+                const int i = (tid + (k0 + k) * NT) * VW, row = (i / TK) * g->stk, cc = i % TK;
+                const uint2 lo = spec_half(srs, i < n_vals ? (row + spec_col(*g, part, cc)) * (int)sizeof(T) : kNoOffset);
+                const uint2 hi =
+                    spec_half(srs, i < n_vals ? (row + spec_col(*g, part, cc + VW / 2)) * (int)sizeof(T) : kNoOffset);
+                piece[k] = {lo.x, lo.y, hi.x, hi.y};
+            } else {
+                piece[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                         srs, (tid + (k0 + k) * NT) * 16, 0, 0));
+            }
+        }
 #pragma unroll
         for (int k = 0; k < CH; ++k) {
             const int i = (tid + (k0 + k) * NT) * VW;    // first value of the piece
@@ -243,8 +283,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
     const bool flip_y = ro.flip_y;
     const bool zc = g.nkz_s < N;
     const int nkz = g.nkz_s;
-    const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)g.C * 6 * nkz * tk;
-    const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * tk * sizeof(T)));
+    const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)g.C * 6 * nkz * g.stk;
+    const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * g.stk * sizeof(T)));
     const int s_lane = (j * tk + c) * (int)sizeof(T);
     const int s_lane_m = ((Tc - j) * tk + c) * (int)sizeof(T);
     // density rows z < nz of the block's columns (rows >= nz read zero; lanes
@@ -288,7 +328,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
         }
     }
     if constexpr (SL) {
-        stage_spectrum_tile<T, NC, TK, TK * Tc>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x);
+        if (g.sratio == 1)
+            stage_spectrum_tile<T, NC, TK, TK * Tc>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x);
+        else
+            stage_spectrum_tile<T, NC, TK, TK * Tc, true, 8>(s_l, split_rsrc(sp, ro, g), nkz, flip_y, g.sgn_y,
+                                                             (int)threadIdx.x, &g, split_part(ro, g));
         __syncthreads();
     }
 #define DDS_LOAD_SPEC(DST, CH)                                                             \
@@ -448,7 +492,7 @@ __global__ void __launch_bounds__(64 * RW) k_z_wave(const cplx<T>* __restrict__ 
     const bool flip_y = ro.flip_y;
     const bool zc = g.nkz_s < N;
     const int nkz = g.nkz_s;
-    const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)g.C * 6 * nkz * TK;
+    const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)g.C * 6 * nkz * TK;
     const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * TK * sizeof(T)));
     T* s_l = reinterpret_cast<T*>(smem_raw);
     const size_t stage_bytes = SL ? ((size_t)nkz * KS * sizeof(T) + 15) / 16 * 16 : 0;
@@ -646,7 +690,7 @@ __global__ void __launch_bounds__(768) k_z_grouped(const cplx<T>* __restrict__ i
     const int nkz = g.nkz_s;
     T sv[OPG][NC][E];
     {
-        const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)g.C * 6 * nkz * tk;
+        const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)g.C * 6 * nkz * tk;
         const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * tk * sizeof(T)));
         const int s_lane = (j * tk + c) * (int)sizeof(T);
         const int s_lane_m = ((Tc - j) * tk + c) * (int)sizeof(T);

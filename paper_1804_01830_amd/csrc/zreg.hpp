@@ -232,8 +232,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     const NyquistRole nq = ro.nq;
     if (nq.skip_block) return;                      // uniform over the block, before any barrier
     const bool flip_y = ro.flip_y;
-    const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)(NC * 6 * PL);
-    const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)(NC * 6 * PL * sizeof(T)));
+    const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)(NC * 6 * NKZ * g.stk);
+    const __amdgpu_buffer_rsrc_t srs = split_rsrc(sp, ro, g);
     // rows z < nz of the lane's column (others: reads give zero, stores are dropped)
     const cplx<T>* in_b = in + ro.in0;
     int r_off[FR ? 1 : EH];
@@ -269,16 +269,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
         }
     }
     {
-        // 16-byte pieces of [c][v - v0][kz][tk], CH loads of a thread in flight
+        // 16-byte pieces of [c][v - v0][kz][tk], CH loads of a thread in flight (halves of
+        // them where the spectrum's tiles are narrower)
         constexpr int P4 = PL / 4, n4 = NC * NV * P4, CH = 8;
         const int nt = (int)blockDim.x;
         for (int i0 = (int)threadIdx.x; i0 < n4; i0 += CH * nt) {
             uint4 piece[CH];
+            if (g.sratio == 1) {
 #pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                const int i = i0 + k * nt, q0 = i / P4, cv = (q0 / NV) * 6 + v0 + q0 % NV;
-                piece[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                         srs, (cv * P4 + i - q0 * P4) * 16, 0, 0));
+                for (int k = 0; k < CH; ++k) {
+                    const int i = i0 + k * nt, q0 = i / P4, cv = (q0 / NV) * 6 + v0 + q0 % NV;
+                    piece[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                             srs, (cv * P4 + i - q0 * P4) * 16, 0, 0));
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < CH; ++k) {
+                    const int i = i0 + k * nt, q0 = i / P4, cv = (q0 / NV) * 6 + v0 + q0 % NV, r = 4 * (i - q0 * P4);
+                    const int row = (cv * NKZ + r / TK) * g.stk, cc = r % TK;
+                    const uint2 lo = spec_half(srs, i < n4 ? (row + spec_col(g, split_part(ro, g), cc)) * 4 : kNoOffset);
+                    const uint2 hi = spec_half(srs, i < n4 ? (row + spec_col(g, split_part(ro, g), cc + 2)) * 4 : kNoOffset);
+                    piece[k] = {lo.x, lo.y, hi.x, hi.y};
+                }
             }
 #pragma unroll
             for (int k = 0; k < CH; ++k) {
