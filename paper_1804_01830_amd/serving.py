@@ -336,8 +336,8 @@ class GpuExecutor:
         """(bytes per shape, bytes per slot): the shape's base plan holds the
         kernel spectrum and its own batch-1 work buffers; a slot holds a
         shared plan's work buffers and its density and stress staging."""
-        cached, work, _ = self.B.footprint(self._desc(key, batch))
-        _, base_work, _ = self.B.footprint(self._desc(key, 1))
+        _, work, _ = self.B.footprint(self._desc(key, batch))
+        cached, base_work, _ = self.B.footprint(self._desc(key, 1))     # (the spectrum's tiles are the base plan's)
         nx, ny, nz = key.n
         elem = 4 if key.precision == 32 else 8
         staging = batch * (key.channels + 6) * nx * ny * nz * elem
