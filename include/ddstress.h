@@ -248,7 +248,7 @@ ddstress_status ddstress_stress(ddstress_plan plan, void* sigma, int32_t where, 
  * alive until the last plan sharing it is destroyed. No device work; plans
  * sharing a spectrum may run concurrently on distinct streams. A call runs the
  * z kernel of its own number of realisations, whatever batch the spectrum was
- * built for (a tuned plan's sharers keep its launch shapes). */
+ * built for; up to a tuned plan's batch its sharers keep its launch shapes. */
 ddstress_status ddstress_plan_share(ddstress_plan src, int32_t batch, ddstress_plan* out);
 
 /* One-shot evaluation of the first `nbatch` (1 <= nbatch <= batch) densities:

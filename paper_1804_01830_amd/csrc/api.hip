@@ -173,7 +173,7 @@ struct ddstress_plan_s {
     int rows_x = 1, tk_y = 1;      // x rows and y columns per block
     int ex = 16, ey = 16, ez = 8;  // element classes of the x, y and fused z passes
     int rows_inv = 1, ex_inv = 16; // the inverse x pass (a tuning's rows and class, or its own defaults)
-    bool tuned = false;            // launch shapes given by the caller
+    int tuned_batch = 0;           // the batch that the caller's launch shapes are for, if any
     bool yx = false;               // inverse y and x as one kernel
     bool xy = false;               // forward x and y as one kernel
     double* plane_stats = nullptr; // Eq. 20 output of every stress call (device), or none
@@ -451,7 +451,8 @@ ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
 // spectrum's tile is the default of the batch that it was built for; a plan that
 // shares it for more realisations runs the kernel and the tile of those (or the
 // widest narrower one that can), whose blocks then copy several spectrum tiles each. A
-// tuned plan keeps its tile, and so do the forms that read the spectrum in place.
+// tuning's tile holds for the batch that it was made for, and the forms that read the
+// spectrum in place keep the spectrum's.
 // us, whole FP32 calls of eight realisations on the spectrum of a plan of one,
 // this tile / the spectrum's own (a plan of eight): three channels 128x128x32 437 / 478 (418),
 // 256x256x32 2046 / 2372 (1999), 128x128x64 865 / 1133 (847); six 592 / 774 (568), 2871 / 3557 (2789), 1232 /
@@ -459,7 +460,7 @@ ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
 // kernel were tried: its scalar registers are short, and one stride more cost it 10 to 20 percent.
 int z_call_tile(const ddstress_plan_s* p, int nb) {
     const Shape& s = p->shape;
-    if (p->tuned || s.zg != 1) return s.tkz;
+    if (nb <= p->tuned_batch || s.zg != 1) return s.tkz;
     for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem); tk > s.tkz; tk /= 2) {
         ZGeom g = z_geom(s, tk, s.tkz, nb, false, false);
         z_launch_plan(s.P[2], p->ez, 1, g, tk, s.elem);
@@ -690,7 +691,7 @@ void create_plan(const ddstress_desc* desc, const ddstress_tuning* tuning, hipSt
         p->tk_y = lc.tk_y;
         p->ey = lc.ey;
         p->ez = lc.ez;
-        p->tuned = tuning != nullptr;
+        p->tuned_batch = tuning ? desc->batch : 0;
         p->yx = lc.yx;
         p->xy = lc.xy;
         const Shape& s = p->shape;
@@ -975,7 +976,7 @@ ddstress_status ddstress_plan_share(ddstress_plan src, int32_t batch, ddstress_p
             p->ex = src->ex;
             p->ey = src->ey;
             p->ez = src->ez;
-            p->tuned = src->tuned;
+            p->tuned_batch = src->tuned_batch;
             p->yx = src->yx;
             p->xy = src->xy;
             p->re_max = src->re_max;

@@ -51,3 +51,29 @@ def test_shared_plans_run_the_form_of_their_batch(n, lines, src, nb):
         assert shared.z_form()[:2] == direct.z_form()[:2]
     shared.close()
     direct.close()
+
+
+@pytest.mark.parametrize("n,lines", [((9, 8, 32), 2), ((20, 8, 64), 1), ((20, 8, 16), 1)])
+def test_a_tuning_holds_for_its_batch(n, lines):
+    """Sharers of a tuned plan run its tile up to its batch, and the form of their own beyond."""
+    import torch
+    from paper_1804_01830_amd import binding as B
+    w = W.random_field(n, batch=4, seed=92, d=(1.0, 1.0, 2.0), n_lines=lines)
+    desc = B.make_desc(w["n"], w["d"], w["mu"], w["nu"], w["lines"], precision=32, batch=4)
+    direct = B.Plan(desc)
+    desc.batch = 1
+    i = B.Plan(desc).info()
+    t = B.Tuning()
+    t.rows_x, t.tk_y, t.ex, t.ey, t.tk_z, t.ez, t.z_groups = (i.rows_x, i.tile_y, i.ex, i.ey, i.tile_z, i.ez, 1)
+    tuned = B.Plan(desc, tuning=t)
+    shared = tuned.share(4)
+    assert shared.z_form(1)[:2] == tuned.z_form()[:2] and tuned.z_form()[1] == t.tk_z
+    assert shared.z_form(4)[:2] == direct.z_form()[:2] and shared.info().tile_z == t.tk_z
+    rho = torch.from_numpy(w["rho"]).to("cuda", dtype=torch.float32).contiguous()
+    ref, out = direct.new_output(), direct.new_output()
+    direct.stress_batch(rho, ref, 4)
+    shared.stress_batch(rho, out, 4)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+    for p in (shared, tuned, direct):
+        p.close()
