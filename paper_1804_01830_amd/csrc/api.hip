@@ -101,6 +101,13 @@ void set_mirrors(Shape& s, bool my, bool mz) {
     s.nkzs = s.mir_z ? s.P[2] / 2 + 1 : s.P[2];
 }
 
+// Bytes that a call on nb realisations touches: its densities and stresses, the
+// spectra of both before and after the fused z pass, and the kernel spectrum.
+int64_t call_bytes(const Shape& s, int nb) {
+    const int64_t fields = (int64_t)nb * (s.C + 6);
+    return s.elem * (fields * s.cells() + fields * 2 * s.N[2] * s.P[1] * s.wx + (int64_t)s.nkys * s.nkzs * s.M1 * 6 * s.C);
+}
+
 Shape make_shape(const ddstress_desc* d) {
     Shape s{};
     for (int a = 0; a < 3; ++a) {
@@ -118,9 +125,9 @@ Shape make_shape(const ddstress_desc* d) {
     // A strip block carries one realisation with one cache line per value;
     // with few realisations it would outlast the other blocks of the launch.
     s.zstrip = s.B >= kZStripBatch;
-    s.tkz = default_z_tk(s.P[2], s.C, s.zg, s.B, s.elem);
-    s.ntz = (s.M1 + s.tkz - 1) / s.tkz;
     set_mirrors(s, predict_mirror(d, 1), predict_mirror(d, 2));
+    s.tkz = default_z_tk(s.P[2], s.C, s.zg, s.B, s.elem, call_bytes(s, s.B));
+    s.ntz = (s.M1 + s.tkz - 1) / s.tkz;
     s.sgn_y = s.sgn_z = 0;
     // The fused z pass addresses a density (or stress) group of Nz Py Wx
     // complex values through buffer resources with 32-bit byte offsets: the
@@ -461,7 +468,7 @@ ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
 int z_call_tile(const ddstress_plan_s* p, int nb) {
     const Shape& s = p->shape;
     if (nb <= p->tuned_batch || s.zg != 1) return s.tkz;
-    for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem); tk > s.tkz; tk /= 2) {
+    for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem, call_bytes(s, nb)); tk > s.tkz; tk /= 2) {
         ZGeom g = z_geom(s, tk, s.tkz, nb, false, false);
         z_launch_plan(s.P[2], p->ez, 1, g, tk, s.elem);
         if (z_retile_ok(s.P[2], g, tk, s.elem)) return tk;

@@ -329,10 +329,15 @@ int default_rows(int M, int elem_bytes) {
     return rows;
 }
 
-int default_z_tk(int N, int C, int groups, int B, int elem_bytes) {
+int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int64_t bytes) {
     if (elem_bytes == 4 && groups == 1 && z_reg_applies(N, C, B)) return z_reg_tile(N);
+    // Two FP32 realisations at length 64, three channels: the wave form's four columns are 32-byte
+    // pieces, which pay within the last cache only. us, whole call, wave form / eight staged columns:
+    // 128x128x32 (248 MB) 104 / 110, 256x64x32 (238) 124 / 127; 128x256x32 (338) 328 / 291, 256x256x32 periodic (361)
+    // 224 / 207, 400x60x30 (424) 287 / 254, 256x256x32 657 / 577.
+    const bool wide = elem_bytes == 4 && N == 64 && C == 3 && B == 2 && bytes > kLastCache;
     // (length 8 in FP64: one realisation 5.9 us against 5.3 in the single-group form, four 8.4 / 12.3)
-    if (groups == 1 && z_wave4_applies(N, C, B, base_ev_z(elem_bytes), 256 / N, elem_bytes) &&
+    if (groups == 1 && !wide && z_wave4_applies(N, C, B, base_ev_z(elem_bytes), 256 / N, elem_bytes) &&
         !(elem_bytes == 8 && N == 8 && B == 1))
         return 256 / N;
     const int tc = N / ecount(N, default_ev_z(N, groups, elem_bytes));
