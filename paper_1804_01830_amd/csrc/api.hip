@@ -126,7 +126,7 @@ Shape make_shape(const ddstress_desc* d) {
     // with few realisations it would outlast the other blocks of the launch.
     s.zstrip = s.B >= kZStripBatch;
     set_mirrors(s, predict_mirror(d, 1), predict_mirror(d, 2));
-    s.tkz = default_z_tk(s.P[2], s.C, s.zg, s.B, s.elem, call_bytes(s, s.B));
+    s.tkz = default_z_tk(s.P[2], s.C, s.zg, s.B, s.elem, s.N[2], call_bytes(s, s.B));
     s.ntz = (s.M1 + s.tkz - 1) / s.tkz;
     s.sgn_y = s.sgn_z = 0;
     // The fused z pass addresses a density (or stress) group of Nz Py Wx
@@ -468,7 +468,7 @@ ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
 int z_call_tile(const ddstress_plan_s* p, int nb) {
     const Shape& s = p->shape;
     if (nb <= p->tuned_batch || s.zg != 1) return s.tkz;
-    for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem, call_bytes(s, nb)); tk > s.tkz; tk /= 2) {
+    for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem, s.N[2], call_bytes(s, nb)); tk > s.tkz; tk /= 2) {
         ZGeom g = z_geom(s, tk, s.tkz, nb, false, false);
         z_launch_plan(s.P[2], p->ez, 1, g, tk, s.elem);
         if (z_retile_ok(s.P[2], g, tk, s.elem)) return tk;

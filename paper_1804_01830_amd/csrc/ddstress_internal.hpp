@@ -214,8 +214,8 @@ bool ev_col_ok(int ev);
 bool ev_z_ok(int N, int ev, int elem_bytes);
 int default_col_tk(int N, int elem_bytes);
 int default_rows(int M, int elem_bytes);
-// `bytes`: a call's densities, stresses, spectrum and hand-over buffers.
-int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int64_t bytes);
+// `nz`: layers; `bytes`: a call's densities, stresses, spectrum and hand-over buffers.
+int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int nz, int64_t bytes);
 constexpr int64_t kLastCache = int64_t(256) << 20;      // the last cache of gfx950
 size_t z_lds_bytes(int N, int tk, int C, int groups, int elem_bytes);
 int z_lds_ld(int tk, int elem_bytes);

@@ -329,7 +329,7 @@ int default_rows(int M, int elem_bytes) {
     return rows;
 }
 
-int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int64_t bytes) {
+int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int nz, int64_t bytes) {
     if (elem_bytes == 4 && groups == 1 && z_reg_applies(N, C, B)) return z_reg_tile(N);
     // Two FP32 realisations at length 64, three channels: the wave form's four columns are 32-byte
     // pieces, which pay within the last cache only. us, whole call, wave form / eight staged columns:
@@ -346,7 +346,13 @@ int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int64_t bytes)
         tk = 128 / tc;
     } else if (N > 256) {
         tk = std::max(elem_bytes <= 4 ? 16 : 8, 256 / tc);
-    } else if (elem_bytes == 4 && N == 64 && C == 3 && B >= 6) {
+    } else if (elem_bytes == 4 && N == 64 && C == 3 && B >= 6 && bytes > 2 * kLastCache && nz > 28) {
+        // Sixteen columns, whole cache lines, where the rows come from HBM and nearly all are data; eight
+        // elsewhere, whose blocks are half as long. us, whole call, 8 / 16: six and eight realisations of
+        // 128x128x32 339 / 333 and 435 / 417, eight of 128x128x30 410 / 399, 100x100x32 415 / 396, 256x256x32 2031 /
+        // 2000 (five of 128x128x32 277 / 274, 256x256x32 1320 / 1319: not taken); within or near the cache, eight of
+        // 64x64x32 96 / 103, 128x128x32 periodic (380 MB) 136 / 145, 128x64x32 (450) 234 / 236; fewer layers, eight of 128x128x28 390 / 388, x24 334 / 357, x20 300 /
+        // 311, 256x256x20 1434 / 1489.
         tk = 16;
     } else {
         // The smallest blocks that still fill the launch: one wave up to length

@@ -26,3 +26,11 @@ def tile(n, lines, precision, batch, periodic=False):
                                                  ((256, 256, 32), False, 8)])
 def test_two_realisations_of_three_channels_at_length_64(n, periodic, expected):
     assert tile(n, 1, 32, 2, periodic) == expected
+
+
+@pytest.mark.parametrize("n,batch,periodic,expected", [((128, 128, 32), 6, False, 16), ((128, 128, 30), 8, False, 16),
+                                                       ((128, 128, 32), 5, False, 8), ((128, 128, 28), 8, False, 8),
+                                                       ((100, 75, 20), 8, False, 8), ((64, 64, 32), 8, False, 8),
+                                                       ((128, 128, 32), 8, True, 8)])
+def test_six_to_eleven_realisations_of_three_channels_at_length_64(n, batch, periodic, expected):
+    assert tile(n, 1, 32, batch, periodic) == expected
