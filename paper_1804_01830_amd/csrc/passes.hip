@@ -354,6 +354,13 @@ int default_z_tk(int N, int C, int groups, int B, int elem_bytes, int nz, int64_
         // 64x64x32 96 / 103, 128x128x32 periodic (380 MB) 136 / 145, 128x64x32 (450) 234 / 236; fewer layers, eight of 128x128x28 390 / 388, x24 334 / 357, x20 300 /
         // 311, 256x256x20 1434 / 1489.
         tk = 16;
+    } else if (elem_bytes == 8 && C == 9 && bytes > 4 * kLastCache && ((N == 32 && B >= 6) || (N == 64 && B >= 12 && nz > 28))) {
+        // Large FP64 batches of nine channels: wider pieces of the rows again. us, whole call, length 32, tile
+        // 4 / 16: 256x256x16 with 8 and 12 realisations 4563 / 4331, 6904 / 6484, 128x128x16 with 12 1814 / 1729,
+        // 100x75x16 with 12 1591 / 1544 (smaller: 64x64x16 with 12 405 / 416, 256x256x16 with 2 1145 / 1196);
+        // length 64, tile 4 / 8: 128x128x32 with 8 and 12 2355 / 2360, 3575 / 3514, 400x60x30 with 12 6331 / 6212,
+        // 100x75x20 with 12 2472 / 2570.
+        tk = N == 32 ? 16 : 8;
     } else {
         // The smallest blocks that still fill the launch: one wave up to length
         // 32, two up to 128, four at 256. More of them run at once and each waits

@@ -34,3 +34,10 @@ def test_two_realisations_of_three_channels_at_length_64(n, periodic, expected):
                                                        ((128, 128, 32), 8, True, 8)])
 def test_six_to_eleven_realisations_of_three_channels_at_length_64(n, batch, periodic, expected):
     assert tile(n, 1, 32, batch, periodic) == expected
+
+
+@pytest.mark.parametrize("n,batch,expected", [((128, 128, 16), 12, 16), ((256, 256, 16), 6, 16), ((256, 256, 16), 5, 4),
+                                              ((64, 64, 16), 12, 4), ((128, 128, 32), 12, 8), ((128, 128, 32), 11, 4),
+                                              ((100, 75, 20), 12, 4)])
+def test_double_precision_batches_of_nine_channels(n, batch, expected):
+    assert tile(n, 3, 64, batch) == expected
