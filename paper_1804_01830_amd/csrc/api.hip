@@ -463,8 +463,7 @@ ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
 // us, whole FP32 calls of eight realisations on the spectrum of a plan of one,
 // this tile / the spectrum's own (a plan of eight): three channels 128x128x32 437 / 478 (418),
 // 256x256x32 2046 / 2372 (1999), 128x128x64 865 / 1133 (847); six 592 / 774 (568), 2871 / 3557 (2789), 1232 /
-// 1527 (1198); nine 811 / 1067 (785), 3926 / 4962 (3846). In-place reads of narrower tiles by the unstaged
-// kernel were tried: its scalar registers are short, and one stride more cost it 10 to 20 percent.
+// 1527 (1198); nine 811 / 1067 (785), 3926 / 4962 (3846).
 int z_call_tile(const ddstress_plan_s* p, int nb) {
     const Shape& s = p->shape;
     if (nb <= p->tuned_batch || s.zg != 1) return s.tkz;

@@ -158,11 +158,13 @@ struct ZGeom {
     int64_t irs, iqs, ios; // input z / plane / ky strides
     int64_t ors, oqs, oos; // output strides (6B planes)
     int strip;             // the spectrum keeps the Nyquist strip where the tiles allow it
-    int stk, snt;          // columns of a spectrum tile, and tiles per stored ky row
-    int sratio, sts;       // spectrum tiles per block, and log2 stk (1 and 31 where the two widths are the same)
-    int nyq, snyq;         // groups of the Nyquist strip, of tk and of stk rows (z_nyq_groups; set by launch_z_fused)
+    int nyq;               // groups of the Nyquist strip (z_nyq_groups; set by launch_z_fused)
     int sb;                // realisations per block of the strip (set by launch_z_fused)
-    int form;              // ZForm of the launch (set by launch_z_fused)
+    int stk, snt;          // columns of a spectrum tile, and tiles per stored ky row
+    // set by launch_z_fused:
+    int form;              // ZForm of the launch
+    int snyq;              // groups of the Nyquist strip in the spectrum's tiles
+    int sratio, sts;       // spectrum tiles per block, and log2 stk (1 and 31 where the two widths are the same)
 };
 // The kernels of the fused z pass (values of ddstress_z_launch.form).
 enum ZForm { kZSerial = 0, kZGrouped = 1, kZWave = 2, kZReg = 3 };
@@ -189,6 +191,9 @@ __host__ __device__ inline int z_nyq_groups(int ncols, int tk, int nky) {
 template <typename T>
 void launch_z_fused(int N, int ev, int groups, const cplx<T>* in, cplx<T>* out, const T* spec, const ZGeom& g,
                     const cplx<T>* tw, int tk, hipStream_t s);
+// Lengths of the single-group form's instances for narrower spectrum tiles: those whose tile
+// depends on the batch.
+constexpr bool z_split_length(int N, int elem_bytes) { return elem_bytes == 4 && N >= 32 && N <= 128; }
 // Whether the launch of z_launch_plan can read a spectrum whose tiles (g.stk) are
 // narrower than its blocks: by the forms that stage the spectrum for base-class
 // transforms, whole tiles a block, in pairs of values or wider, the Nyquist strip

@@ -629,7 +629,7 @@ ZLaunch z_launch_plan(int N, int ev, int groups, ZGeom& g, int tk, int elem_byte
 bool z_retile_ok(int N, const ZGeom& g, int tk, int elem_bytes) {
     const bool pow2 = (tk & (tk - 1)) == 0 && (g.stk & (g.stk - 1)) == 0;
     return pow2 && tk > g.stk && g.stk * elem_bytes >= 8 &&
-           (g.form == kZReg || (g.form == kZSerial && z_stage_spec(N, tk, g.C, g.nkz_s, g.B, elem_bytes))) &&
+           (g.form == kZReg || (g.form == kZSerial && z_split_length(N, elem_bytes) && z_stage_spec(N, tk, g.C, g.nkz_s, g.B, elem_bytes))) &&
            (g.nyq > 0) == (g.snyq > 0);
 }
 

@@ -74,7 +74,7 @@ __device__ __forceinline__ int z_logical_block(const ZGeom& g, int split = 1) {
     return b < strip ? b : strip + xcd_block(b - strip, (int)gridDim.x - strip);
 }
 struct ZRoles {
-    int tile, kyc;        // spectrum tile (the first of g.sratio) and stored row
+    int tile, kyc;        // spectrum tile (SPLIT: the first of g.sratio narrower ones) and stored row
     int parts, stride;    // spectrum tiles of the block that there are, and tiles from one to the next
     bool flip_y;          // row kyc is the y mirror of the block's ky (odd planes change sign)
     int64_t in0;          // offset of the block's first input column in a density plane
@@ -87,7 +87,7 @@ struct ZRoles {
     int b0, b1;           // realisations of the block
     NyquistRole nq;
 };
-template <typename T>
+template <typename T, bool SPLIT = false>
 __device__ __forceinline__ ZRoles z_roles(int blk, int tk, int c, const ZGeom& g) {
     ZRoles r;
     const int tiles = g.nyq > 0 ? g.ntiles - 1 : g.ntiles;
@@ -101,10 +101,10 @@ __device__ __forceinline__ ZRoles z_roles(int blk, int tk, int c, const ZGeom& g
         const bool valid = 2 * ky <= g.nky;
         const int kyv = valid ? ky : q * tk;
         r.flip_y = false;
-        r.tile = g.snt - 1;
-        r.kyc = q * g.sratio;
-        r.parts = min(g.sratio, g.snyq - r.kyc);
-        r.stride = g.snt;                        // (the strip's tiles are one to a stored row)
+        r.tile = SPLIT ? g.snt - 1 : g.ntiles - 1;
+        r.kyc = SPLIT ? q * g.sratio : q;
+        r.parts = SPLIT ? min(g.sratio, g.snyq - r.kyc) : 1;
+        r.stride = SPLIT ? g.snt : 1;            // (the strip's tiles are one to a stored row)
         r.in0 = (int64_t)q * tk * g.ios + m;
         r.lane_in = valid ? c * (int)g.ios : 0;
         r.own = (int64_t)kyv * g.oos + m;
@@ -125,8 +125,8 @@ __device__ __forceinline__ ZRoles z_roles(int blk, int tk, int c, const ZGeom& g
     r.b1 = g.B;
     r.flip_y = g.nky_s < g.nky && 2 * ky > g.nky;
     r.kyc = r.flip_y ? g.nky - ky : ky;
-    r.tile = tile * g.sratio;
-    r.parts = min(g.sratio, g.snt - r.tile);
+    r.tile = SPLIT ? tile * g.sratio : tile;
+    r.parts = SPLIT ? min(g.sratio, g.snt - r.tile) : 1;
     r.stride = 1;
     r.in0 = (int64_t)ky * g.ios + (int64_t)tile * tk;
     r.lane_in = valid ? c : 0;
@@ -255,7 +255,8 @@ __device__ __forceinline__ void stage_spectrum_tile(T* s_l, __amdgpu_buffer_rsrc
 // and reads the spectrum from memory for each realisation. Fewer threads per
 // column than the grouped form: better for few realisations.
 // ----------------------------------------------------------------------------
-template <typename T, int N, int E, int NC, int TK>
+// SPLIT (staged): the spectrum's tiles are narrower than the block's.
+template <typename T, int N, int E, int NC, int TK, bool SPLIT = false>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0 && NC == 3 ? 3 : 1))) k_z_serial(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out,
                                                   const T* __restrict__ spec, ZGeom g,
                                                   const cplx<T>* __restrict__ tw, int tk_arg, int ld_arg) {
@@ -271,7 +272,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
     const int c = threadIdx.x % tk;
     const int j = threadIdx.x / tk;
     const int blk = z_logical_block(g);
-    const ZRoles ro = z_roles<T>(blk, tk, c, g);
+    const ZRoles ro = z_roles<T, SPLIT>(blk, tk, c, g);
     const NyquistRole nq = ro.nq;
     if (nq.skip_block) return;                   // uniform over the block, before any barrier
     const ColMajor lay{ld};
@@ -283,8 +284,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
     const bool flip_y = ro.flip_y;
     const bool zc = g.nkz_s < N;
     const int nkz = g.nkz_s;
-    const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)g.C * 6 * nkz * g.stk;
-    const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * g.stk * sizeof(T)));
+    const T* sp = spec + ((int64_t)ro.kyc * (SPLIT ? g.snt : g.ntiles) + ro.tile) * (int64_t)g.C * 6 * nkz * (SPLIT ? g.stk : tk);
+    const __amdgpu_buffer_rsrc_t srs =
+        SPLIT ? split_rsrc(sp, ro, g) : make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * tk * sizeof(T)));
     const int s_lane = (j * tk + c) * (int)sizeof(T);
     const int s_lane_m = ((Tc - j) * tk + c) * (int)sizeof(T);
     // density rows z < nz of the block's columns (rows >= nz read zero; lanes
@@ -328,11 +330,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TK > 0
         }
     }
     if constexpr (SL) {
-        if (g.sratio == 1)
-            stage_spectrum_tile<T, NC, TK, TK * Tc>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x);
+        if constexpr (SPLIT)
+            stage_spectrum_tile<T, NC, TK, TK * Tc, true, 8>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x, &g,
+                                                             split_part(ro, g));
         else
-            stage_spectrum_tile<T, NC, TK, TK * Tc, true, 8>(s_l, split_rsrc(sp, ro, g), nkz, flip_y, g.sgn_y,
-                                                             (int)threadIdx.x, &g, split_part(ro, g));
+            stage_spectrum_tile<T, NC, TK, TK * Tc>(s_l, srs, nkz, flip_y, g.sgn_y, (int)threadIdx.x);
         __syncthreads();
     }
 #define DDS_LOAD_SPEC(DST, CH)                                                             \
@@ -492,7 +494,7 @@ __global__ void __launch_bounds__(64 * RW) k_z_wave(const cplx<T>* __restrict__ 
     const bool flip_y = ro.flip_y;
     const bool zc = g.nkz_s < N;
     const int nkz = g.nkz_s;
-    const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)g.C * 6 * nkz * TK;
+    const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)g.C * 6 * nkz * TK;
     const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * TK * sizeof(T)));
     T* s_l = reinterpret_cast<T*>(smem_raw);
     const size_t stage_bytes = SL ? ((size_t)nkz * KS * sizeof(T) + 15) / 16 * 16 : 0;
@@ -690,7 +692,7 @@ __global__ void __launch_bounds__(768) k_z_grouped(const cplx<T>* __restrict__ i
     const int nkz = g.nkz_s;
     T sv[OPG][NC][E];
     {
-        const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)g.C * 6 * nkz * tk;
+        const T* sp = spec + ((int64_t)ro.kyc * g.ntiles + ro.tile) * (int64_t)g.C * 6 * nkz * tk;
         const __amdgpu_buffer_rsrc_t srs = make_rsrc(sp, (uint32_t)((size_t)g.C * 6 * nkz * tk * sizeof(T)));
         const int s_lane = (j * tk + c) * (int)sizeof(T);
         const int s_lane_m = ((Tc - j) * tk + c) * (int)sizeof(T);
@@ -804,6 +806,13 @@ static void z_launch(int64_t blocks, int tk, const cplx<T>* in, cplx<T>* out, co
             const dim3 grid((unsigned)blocks);
             const auto staged = [&](auto tkc) {
                 constexpr int TK = decltype(tkc)::value;
+                if constexpr (z_split_length(L, (int)sizeof(T))) {
+                    if (tk != g.stk) {
+                        hipLaunchKernelGGL((k_z_serial<T, L, E, NC, TK, true>), grid, block, lds, s, in, out, spec, g, tw,
+                                           tk, ld);
+                        return;
+                    }
+                }
                 if constexpr (!(sizeof(T) == 8 && E == 2 && L >= 8 && L <= 128 && TK * L == 256))
                     hipLaunchKernelGGL((k_z_serial<T, L, E, NC, TK>), grid, block, lds, s, in, out, spec, g, tw, tk, ld);
                 else    // (the wave form's shapes: no instance)

@@ -190,7 +190,8 @@ __device__ __forceinline__ void lane_fft(cplx<float> (&v)[E], TW&& W) {
 // ... on its own, with no barrier after the copy. Lane p tk + c holds rows
 // z = p + LP m of column c. ZM: only kz <= N / 2 is stored and register
 // m >= E / 2 reads row N - kz. FR: all N / 2 rows are data (nz = N / 2), one
-// row offset instead of one per register.
+// row offset instead of one per register. SPLIT: the spectrum's tiles are narrower
+// than the block's.
 // VG = 0: the C channel spectra stay in registers and the six stress
 // components are formed and transformed back one after the other. VG > 0: a
 // block takes VG components, whose accumulators stay in registers while the
@@ -208,7 +209,7 @@ __device__ __forceinline__ void lane_fft(cplx<float> (&v)[E], TW&& W) {
 // take 503. Two waves per SIMD (up to 256 registers) cover what latency is
 // left; three would spill the accumulators.
 // ----------------------------------------------------------------------------
-template <int N, int LP, int NC, bool ZM, int VG, bool FR>
+template <int N, int LP, int NC, bool ZM, int VG, bool FR, bool SPLIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     k_z_reg(const cplx<float>* __restrict__ in, cplx<float>* __restrict__ out, const float* __restrict__ spec, ZGeom g,
             const cplx<float>* __restrict__ tw) {
@@ -227,13 +228,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
     constexpr int VS = VG > 0 ? 6 / VG : 1;         // blocks per tile
     constexpr int NV = VG > 0 ? VG : 6;             // components of this block: v0 .. v0 + NV - 1
     const int lb = z_logical_block(g, VS);
-    const ZRoles ro = z_roles<T>(lb / VS, TK, c, g);
+    const ZRoles ro = z_roles<T, SPLIT>(lb / VS, TK, c, g);
     const int v0 = (lb % VS) * NV;
     const NyquistRole nq = ro.nq;
     if (nq.skip_block) return;                      // uniform over the block, before any barrier
     const bool flip_y = ro.flip_y;
-    const T* sp = spec + ((int64_t)ro.kyc * g.snt + ro.tile) * (int64_t)(NC * 6 * NKZ * g.stk);
-    const __amdgpu_buffer_rsrc_t srs = split_rsrc(sp, ro, g);
+    const T* sp = spec + ((int64_t)ro.kyc * (SPLIT ? g.snt : g.ntiles) + ro.tile) * (int64_t)(NC * 6 * NKZ * (SPLIT ? g.stk : TK));
+    const __amdgpu_buffer_rsrc_t srs = SPLIT ? split_rsrc(sp, ro, g) : make_rsrc(sp, (uint32_t)(NC * 6 * PL * sizeof(T)));
     // rows z < nz of the lane's column (others: reads give zero, stores are dropped)
     const cplx<T>* in_b = in + ro.in0;
     int r_off[FR ? 1 : EH];
@@ -275,7 +276,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
         const int nt = (int)blockDim.x;
         for (int i0 = (int)threadIdx.x; i0 < n4; i0 += CH * nt) {
             uint4 piece[CH];
-            if (g.sratio == 1) {
+            if constexpr (!SPLIT) {
 #pragma unroll
                 for (int k = 0; k < CH; ++k) {
                     const int i = i0 + k * nt, q0 = i / P4, cv = (q0 / NV) * 6 + v0 + q0 % NV;
@@ -428,14 +429,17 @@ void z_reg_launch(int64_t blocks, const cplx<float>* in, cplx<float>* out, const
         fail(DDSTRESS_E_UNSUPPORTED, "fused z register form: grid or spectrum tile too large");
     const dim3 grid((unsigned)blocks), block(64 * z_reg_waves(g.B));
     const bool full = g.nz == N / 2;                // every row of the unpadded half is a data row
-#define DDS_Z_REG(ZMV, FRV)                                                                                    \
-    hipLaunchKernelGGL((k_z_reg<N, LP, NC, ZMV, VG, FRV>), grid, block, lds, s, in, out, spec, g, tw)
-    if (g.nkz_s < N) {
-        if (full) DDS_Z_REG(true, true);
-        else DDS_Z_REG(true, false);
+#define DDS_Z_REG(ZMV, FRV, SPLITV)                                                                            \
+    hipLaunchKernelGGL((k_z_reg<N, LP, NC, ZMV, VG, FRV, SPLITV>), grid, block, lds, s, in, out, spec, g, tw)
+    if (g.stk != z_reg_tile(N)) {
+        if (g.nkz_s < N) DDS_Z_REG(true, false, true);
+        else DDS_Z_REG(false, false, true);
+    } else if (g.nkz_s < N) {
+        if (full) DDS_Z_REG(true, true, false);
+        else DDS_Z_REG(true, false, false);
     } else {
-        if (full) DDS_Z_REG(false, true);
-        else DDS_Z_REG(false, false);
+        if (full) DDS_Z_REG(false, true, false);
+        else DDS_Z_REG(false, false, false);
     }
 #undef DDS_Z_REG
 }
