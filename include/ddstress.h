@@ -157,7 +157,9 @@ typedef struct {
  * classes change the radix sequence and hence the rounding (within the
  * stated tolerances). */
 typedef struct {
-    int32_t rows_x;        /* rows per block of the x passes (forward and inverse) */
+    int32_t rows_x;        /* rows per block of the x passes. Where class 16 is the faster one forward but not
+                              back (half lengths Px/2 of 128 to 512), ex = 16 runs the inverse pass with class 8
+                              on half of these rows: the same threads, and the same bits */
     int32_t tk_y;          /* consecutive kx columns per block of the y passes */
     int32_t tk_z;          /* consecutive kx columns per block of the fused z pass */
     int32_t ex, ey, ez;    /* element classes of the x, y and fused z passes (0: default) */

@@ -655,10 +655,22 @@ bool yx_request_ok(const Shape& s) {
     return yx_ok(s) && s.elem == 4 && s.P[1] == 256 && s.M == 128 && s.N[1] <= s.P[1] / 2;
 }
 
+// The inverse x pass that goes with a forward one of class ex on `rows` rows: the
+// same, or where class 16 is the slower one for it (default_ev_c2r) class 8 on half
+// the rows, the same threads and the same bits.
+struct XInverse {
+    int rows, ev;
+};
+XInverse x_inverse(int M, int rows, int ex) {
+    const int ev = std::min(ex, default_ev_c2r(M));
+    return {ev == ex ? rows : std::max(1, rows / 2), ev};
+}
+
 LaunchChoice default_launch(const Shape& s) {
-    const int rows = default_rows(s.M, s.elem), ex = default_ev_col(s.M), inv = default_ev_c2r(s.M);
+    const int rows = default_rows(s.M, s.elem), ex = default_ev_col(s.M);
+    const XInverse inv = x_inverse(s.M, rows, ex);
     return {rows, ex, default_col_tk(s.P[1], s.elem), default_ev_y(s.P[1], s.elem), default_ev_z(s.P[2], s.zg, s.elem),
-            s.zg, yx_ok(s), yx_ok(s), inv == ex ? rows : std::max(1, rows / 2), inv};
+            s.zg, yx_ok(s), yx_ok(s), inv.rows, inv.ev};
 }
 
 // Apply a tuning (zero element classes select the defaults) after checking it.
@@ -673,8 +685,9 @@ LaunchChoice apply_tuning(Shape& s, const ddstress_tuning* t) {
     if (t->yx < 0 || t->yx > 2 || (t->yx == 2 && !yx_request_ok(s)) || t->xy < 0 || t->xy > 2 ||
         (t->xy == 2 && !yx_request_ok(s)))
         fail(DDSTRESS_E_INVALID, "fused x-y passes do not apply to this shape");
+    const XInverse inv = x_inverse(s.M, t->rows_x, ex);
     c = {t->rows_x, ex, t->tk_y, ey, ez, zg, t->yx == 0 ? yx_ok(s) : t->yx == 2, t->xy == 0 ? yx_ok(s) : t->xy == 2,
-         t->rows_x, ex};
+         inv.rows, inv.ev};
     s.zg = zg;
     s.tkz = t->tk_z;
     s.ntz = (s.M1 + s.tkz - 1) / s.tkz;
@@ -796,9 +809,10 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
     for (int ev : {8, 16})
         for (int r = 1; r <= kMaxThreads; r *= 2) {
             if (!rows_ok(s, r, ev) || (ev == 16 && s.M <= 8)) continue;
+            const XInverse inv = x_inverse(s.M, r, ev);
             float ms = time_median(st, reps, [&] {
                 launch_x_r2c<T>(s.M, ev, rho.as<T>(), w1.as<cplx<T>>(), BC * Nz * Ny, Nx, Nx, s.wx, twp, r, st);
-                launch_x_c2r<T>(s.M, ev, w2.as<cplx<T>>(), sig.as<T>(), B6 * Nz * Ny, Nx, s.wx, Nx, twp, r, st);
+                launch_x_c2r<T>(s.M, inv.ev, w2.as<cplx<T>>(), sig.as<T>(), B6 * Nz * Ny, Nx, s.wx, Nx, twp, inv.rows, st);
             });
             if (verbose) std::fprintf(stderr, "[tune] x rows=%d ev=%d %.5f ms\n", r, ev, ms);
             if (ms < best) { best = ms; out->rows_x = r; out->ex = ev; out->ms[0] = ms; }
@@ -841,10 +855,11 @@ void autotune_impl(const ddstress_desc* desc, hipStream_t st, ddstress_tuning* o
         {
             const int fuse = yx_request_ok(s) ? 2 : 0;       // by name, or as the default
             const ColGeom gi = inv_y_geom(s, B6);
+            const XInverse inv = x_inverse(s.M, out->rows_x, out->ex);
             const float sep = time_median(st, reps, [&] {
                 launch_col_fft<T>(Py, out->ey, false, w1.as<cplx<T>>(), w2.as<cplx<T>>(), gi, twp, out->tk_y, st);
-                launch_x_c2r<T>(s.M, out->ex, w2.as<cplx<T>>(), sig.as<T>(), B6 * Nz * Ny, Nx, s.wx, Nx, twp,
-                                out->rows_x, st);
+                launch_x_c2r<T>(s.M, inv.ev, w2.as<cplx<T>>(), sig.as<T>(), B6 * Nz * Ny, Nx, s.wx, Nx, twp,
+                                inv.rows, st);
             });
             const float fused = time_median(st, reps, [&] {
                 launch_yx_inv<T>(Py, s.M, w1.as<cplx<T>>(), sig.as<T>(), B6 * Nz, Ny, Nx, s.wx, twp, st, nullptr, Nz);

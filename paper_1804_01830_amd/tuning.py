@@ -18,7 +18,7 @@ def cache_path():
 
 
 # Part of every key: entries written for other launch-shape fields are not reused.
-LAYOUT = "z5"
+LAYOUT = "z6"
 
 
 def device_tag():
