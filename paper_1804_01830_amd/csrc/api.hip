@@ -678,7 +678,9 @@ LaunchChoice apply_tuning(Shape& s, const ddstress_tuning* t) {
     LaunchChoice c = default_launch(s);
     if (!t) return c;
     const int zg = t->z_groups ? t->z_groups : c.zg;
-    const int ex = t->ex ? t->ex : c.ex, ey = t->ey ? t->ey : default_ev_col(s.P[1]);
+    const int ex = t->ex ? t->ex : c.ex;
+    // (the default class, unless only the wider one fits this tile)
+    const int ey = t->ey ? t->ey : col_ok(s, s.P[1], t->tk_y, c.ey) ? c.ey : default_ev_col(s.P[1]);
     const int ez = t->ez ? t->ez : default_ev_z(s.P[2], zg, s.elem);
     if (!rows_ok(s, t->rows_x, ex) || !col_ok(s, s.P[1], t->tk_y, ey) || !z_ok(s, t->tk_z, ez, zg))
         fail(DDSTRESS_E_INVALID, "tuning choice outside the launch limits of this shape");
