@@ -133,8 +133,9 @@ typedef struct {
     int32_t rows_x;        /* rows per block of the x passes */
     int32_t ex, ey, ez;    /* element classes of the x, y and fused z passes (see ddstress_tuning) */
     int32_t z_groups;      /* thread groups per column tile of the fused z pass (see ddstress_tuning) */
-    int32_t yx_fused;      /* 1: inverse y and inverse x run as one kernel (see ddstress_tuning) */
-    int32_t xy_fused;      /* 1: forward x and forward y run as one kernel (see ddstress_tuning) */
+    int32_t yx_fused;      /* 1: inverse y and inverse x run as one kernel (see ddstress_tuning) in every call
+                              whose planes (nbatch * 6 * Nz) are enough for it to pay */
+    int32_t xy_fused;      /* 1: forward x and forward y (nbatch * C * Nz planes), the same */
     int32_t mirror_y;      /* 1: every coefficient plane is even or odd under y -> -y (each line direction
                               has t_y = 0 or is parallel to e_y), so the spectrum is kept for ky <= Py/2
                               only, with a sign per plane for the mirrored rows */
@@ -167,7 +168,8 @@ typedef struct {
     int32_t yx;            /* inverse y and x: 1 two passes, 2 one fused kernel that keeps each
                               (realisation, component, z) plane in LDS (by name for FP32 with Py = 256,
                               Px = 256 and an open y axis only), 0 default (fused wherever a plane
-                              fits: 16 <= Py <= 128 and 16 <= Px <= 256, or the FP32 planes above) */
+                              fits, 16 <= Py <= 128 and 16 <= Px <= 256 or the FP32 planes above, and a call
+                              has planes enough) */
     int32_t xy;            /* forward x and y: 1 two passes, 2 one fused kernel (same shapes), 0 default */
     float   ms[3];         /* autotune: median device ms of the chosen x pair, y pair and z pass */
 } ddstress_tuning;

@@ -481,6 +481,16 @@ struct StatsTarget {
 };
 StatsTarget plan_stats(const ddstress_plan_s* p);
 
+// Whether a call on nb realisations runs the fused forward (inverse) x-y kernel.
+bool call_xy(const ddstress_plan_s* p, int nb) {
+    const Shape& s = p->shape;
+    return p->xy && (int64_t)nb * s.C * s.N[2] >= plane_min(false, s.P[1], s.M, s.N[1], s.elem);
+}
+bool call_yx(const ddstress_plan_s* p, int nb) {
+    const Shape& s = p->shape;
+    return p->yx && (int64_t)nb * 6 * s.N[2] >= plane_min(true, s.P[1], s.M, s.N[1], s.elem);
+}
+
 template <typename T>
 void enqueue_pass(ddstress_plan_s* p, int k, const T* rho, T* sigma, int nb, hipStream_t st,
                   StatsTarget stt) {
@@ -492,7 +502,7 @@ void enqueue_pass(ddstress_plan_s* p, int k, const T* rho, T* sigma, int nb, hip
     const int64_t BC = (int64_t)s.B * s.C;
     const int64_t B6 = (int64_t)s.B * 6;
     const int Nx = s.N[0], Ny = s.N[1], Nz = s.N[2], Py = s.P[1];
-    const bool xy = p->xy, yx = p->yx;
+    const bool xy = call_xy(p, nb), yx = call_yx(p, nb);
     if (k == 0) {
         if (xy) {
             launch_xy_fwd<T>(Py, s.M, rho, w2, BC * Nz, Ny, Nx, s.wx, tw, st, Nz);   // ky-major
@@ -535,9 +545,10 @@ StatsTarget plan_stats(const ddstress_plan_s* p) {
     return {p->plane_stats ? p->rowsq.as<double>() : nullptr, p->plane_stats};
 }
 
-// Whether pass k runs inside the previous pass's kernel (and enqueues nothing).
-bool pass_fused_away(const ddstress_plan_s* p, int k) {
-    return (k == 1 && p->xy) || (k == 4 && p->yx);
+// Whether pass k of a call on nb realisations runs inside the previous pass's kernel
+// (and enqueues nothing).
+bool pass_fused_away(const ddstress_plan_s* p, int k, int nb) {
+    return (k == 1 && call_xy(p, nb)) || (k == 4 && call_yx(p, nb));
 }
 
 template <typename T>
@@ -545,7 +556,7 @@ void run_stress(ddstress_plan_s* p, const T* rho, T* sigma, int nb, hipStream_t 
     p->mark(st);
     for (int k = 0; k < 5; ++k) {
         enqueue_pass<T>(p, k, rho, sigma, nb, st, plan_stats(p));
-        if (pass_fused_away(p, k)) p->mark_fused();     // no event: its time shows as zero
+        if (pass_fused_away(p, k, nb)) p->mark_fused();     // no event: its time shows as zero
         else p->mark(st);
     }
 }
@@ -1091,7 +1102,7 @@ ddstress_status ddstress_plan_z_form(ddstress_plan plan, int32_t nbatch, ddstres
         if (nbatch < 1 || nbatch > plan->shape.B) fail(DDSTRESS_E_INVALID, "nbatch must lie in [1, batch]");
         const Shape& s = plan->shape;
         const int tk = z_call_tile(plan, nbatch);
-        ZGeom g = z_geom(s, tk, s.tkz, nbatch, plan->xy, plan->yx);
+        ZGeom g = z_geom(s, tk, s.tkz, nbatch, call_xy(plan, nbatch), call_yx(plan, nbatch));
         const ZLaunch l = z_launch_plan(s.P[2], plan->ez, s.zg, g, tk, s.elem);
         *out = {l.form, tk, l.threads, l.blocks};
     });
@@ -1137,7 +1148,7 @@ ddstress_status ddstress_plan_time_passes(ddstress_plan plan, void* sigma, int32
             for (auto& e : ev) check_hip(hipEventCreate(&e), "event create");
             for (int k = 0; k < 5; ++k) {
                 check_hip(hipEventRecord(ev[2 * k], st), "event record");
-                if (!pass_fused_away(plan, k))
+                if (!pass_fused_away(plan, k, plan->shape.B))
                     for (int r = 0; r < reps; ++r) {
                         if (plan->shape.elem == 4)
                             enqueue_pass<float>(plan, k, static_cast<const float*>(plan->rho),
@@ -1152,7 +1163,7 @@ ddstress_status ddstress_plan_time_passes(ddstress_plan plan, void* sigma, int32
             for (int k = 0; k < 5; ++k) {
                 float t = 0.f;
                 check_hip(hipEventElapsedTime(&t, ev[2 * k], ev[2 * k + 1]), "event time");
-                ms[k] = pass_fused_away(plan, k) ? 0.0 : (double)t / reps;
+                ms[k] = pass_fused_away(plan, k, plan->shape.B) ? 0.0 : (double)t / reps;
             }
         } catch (...) {
             for (auto& e : ev)

@@ -259,6 +259,7 @@ void z_dispatch(int N, int ev, const cplx<T>* in, cplx<T>* out, const T* spec, c
 // interleaved in groups of zp: plane p starts at (p / zp) zp Py wx + (p % zp) wx
 // and its rows are zp wx apart (zp = 1: each plane contiguous).
 bool plane_fits(int Py, int M, int ny, int elem_bytes);
+int64_t plane_min(bool inverse, int Py, int M, int ny, int elem_bytes);   // planes from which a launch of them pays
 inline void check_plane_launch(int64_t nplanes, int zp) {
     if (nplanes > 0x7fffffffLL) fail(DDSTRESS_E_UNSUPPORTED, "grid too large for one launch");
     if (zp < 1 || nplanes % zp != 0) fail(DDSTRESS_E_INVALID, "plane interleave must divide the plane count");

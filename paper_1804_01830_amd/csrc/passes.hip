@@ -491,6 +491,29 @@ bool plane_fits(int Py, int M, int ny, int elem_bytes) {
     return vals * 2 * elem_bytes <= (size_t)160 * 1024;
 }
 
+// The fewest planes of a launch with which the fused kernels beat the separate
+// passes. A plane is one block, and at Py = 128 its chain of row passes and of 32
+// values per lane is long: with fewer planes than a part of the CUs the separate
+// passes, which split a plane, are through earlier. That is so in FP64 and on full
+// columns (periodic y, ny > 64); elsewhere fused is faster from the first plane on.
+// One realisation, whole call in us, fused / separate, by planes of the launch:
+//   forward, FP64, M = 128: 100x64x4 (12) 43.4 / 40.6, x16 (48) 52.4 / 51.9, 128x40x16 (48) 48.1 / 48.5
+//   forward, full columns: FP64 128x128x4 (12) 36.7 / 33.8, x16 (48) 45.1 / 43.2, three of x8 (72) 50.1 / 51.5; FP32
+//     128x128x4 28.6 / 27.0, x16 34.9 / 34.1, (72) 41.3 / 42.2; FP64 256x64x1 (3) 27.5 / 25.0, x4 (12) 30.7 / 28.6, x8 (24)
+//     34.1 / 34.2
+//   inverse, FP64: 30x64x8 (48) 27.9 / 26.9, x16 (96) 32.9 / 32.1, (144) 38.4 / 40.6; 16x50x16 (96) 28.3 / 26.9, (144) 31.9 / 31.1;
+//     100x64x8 (48) 47.4 / 45.3, (60) 52.1 / 51.4, (96) 52.4 / 54.7; 64x64x2 27.4 / 25.5, x8 32.5 / 31.9, (60) 36.6 / 36.4
+//   inverse, full columns, FP32: 32x128x16 (96) 26.2 / 25.7, 64x128 (60) 27.7 / 27.0, (96) 29.2 / 29.1, 128x128x8 (48) 30.1 / 29.5,
+//     (96) 34.9 / 37.1, 256x128x4 (24) 37.1 / 36.1, x8 (48) 40.4 / 41.0
+int64_t plane_min(bool inverse, int Py, int M, int ny, int elem_bytes) {
+    const bool full = ny > Py / 2, fp64 = elem_bytes == 8;
+    if (M < 16 || (Py != 128 && !(Py == 64 && full && fp64 && M == 128 && !inverse))) return 0;
+    if (Py == 64) return 16;
+    if (!inverse) return full ? 64 : fp64 && M == 128 ? 48 : 0;
+    if (fp64) return M == 16 ? 160 : M == 32 ? 112 : 64;
+    return !full ? 0 : M == 16 ? 112 : M == 32 ? 80 : M == 64 ? 64 : 32;
+}
+
 // Real rows can be accessed in pairs when every row starts on a pair boundary.
 template <typename T>
 static int pairs_ok(const T* base, int64_t stride, int n) {
