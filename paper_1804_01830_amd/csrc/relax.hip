@@ -147,7 +147,10 @@ __device__ __forceinline__ void ghost_value(const T* __restrict__ u, const T* __
 // The ghost planes are not read: the blocks of the surface chunks form theirs
 // from the real layers (Eq. 18b) while their first planes are on the way. For that
 // the last chunk marches downwards, so that a ghost plane is always a block's
-// first one (there are at least two chunks).
+// first one (there are at least two chunks). FORMED: the state's ghost planes are there and
+// are read like any other (the first step of a call; forming them takes a thin film's step
+// a tenth longer: 512 x 512 x 16 FP64 one step and its ghost launch 65.9 us against 68.0,
+// 128 x 128 x 32 13.6 against 15.2).
 //
 // STREAM: the force, read once a step, does not displace the displacements in
 // the caches.
@@ -157,7 +160,7 @@ __device__ __forceinline__ void ghost_value(const T* __restrict__ u, const T* __
 // two barriers a layer and a ghost launch a step it was 31.1); FP64, 308 MB, 55 us
 // (66). A second plane requested ahead was no faster (27.3). Small films are bound
 // by the launch and its two memory latencies: 70 x 33 x 12 FP64 5.6 us a step (9.7).
-template <typename T, int TX, int TY, bool STREAM>
+template <typename T, int TX, int TY, bool STREAM, bool FORMED>
 __global__ void __launch_bounds__(TX* TY)
     k_relax_march(const T* __restrict__ u, T* __restrict__ un, const T* __restrict__ f, const T* __restrict__ phi,
                   RelaxGeom<T> g, int tiles_x, int nchunks, int kc) {
@@ -240,7 +243,7 @@ __global__ void __launch_bounds__(TX* TY)
         fetch(mid, kf + 1);
         fetch(pre, kf + 1 + dir);
         fetch_force(fn, kf);
-        if (down || chunk == 0) {
+        if (!FORMED && (down || chunk == 0)) {
 #pragma unroll
             for (int q = 0; q < PER; ++q)
                 if (t + q * NT < PL) {
@@ -471,15 +474,20 @@ struct ddstress_relax_s {
         check_hip(hipGetLastError(), "relaxation ghost launch");
         cur = 0;
     }
-    // One step from a into b, in z chunks so that about `target` blocks run.
+    // One step from a into b, in z chunks so that about `target` blocks run. formed: a's ghost
+    // layers are there (those of the state that a call starts from).
     template <typename T, int TX, int TY, bool STREAM>
-    void march(const T* a, T* b, const RelaxGeom<T>& g, int target, hipStream_t st) {
+    void march(const T* a, T* b, const RelaxGeom<T>& g, int target, bool formed, hipStream_t st) {
         const int tiles_x = (desc.n[0] + TX - 1) / TX, tiles = tiles_x * ((desc.n[1] + TY - 1) / TY);
         int nchunks = std::max(2, std::min(desc.n[2], (target + tiles - 1) / tiles));
         const int kc = (desc.n[2] + nchunks - 1) / nchunks;
         nchunks = (desc.n[2] + kc - 1) / kc;
-        hipLaunchKernelGGL((k_relax_march<T, TX, TY, STREAM>), dim3((unsigned)(tiles * nchunks)), dim3(TX * TY), 0, st, a,
-                           b, f.as<T>(), phi.as<T>(), g, tiles_x, nchunks, kc);
+        const auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * nchunks)), dim3(TX * TY), 0, st, a, b, f.as<T>(), phi.as<T>(),
+                               g, tiles_x, nchunks, kc);
+        };
+        if (formed) launch(k_relax_march<T, TX, TY, STREAM, true>);
+        else launch(k_relax_march<T, TX, TY, STREAM, false>);
         check_hip(hipGetLastError(), "relaxation step launch");
     }
     template <typename T>
@@ -495,8 +503,8 @@ struct ddstress_relax_s {
         for (int s = 0; s < n; ++s) {
             const T* a = u[cur].as<T>();
             T* b = u[cur ^ 1].as<T>();
-            if (large) stream ? march<T, 128, 8, true>(a, b, g, 256, st) : march<T, 128, 8, false>(a, b, g, 256, st);
-            else stream ? march<T, 64, 4, true>(a, b, g, 1024, st) : march<T, 64, 4, false>(a, b, g, 1024, st);
+            if (large) stream ? march<T, 128, 8, true>(a, b, g, 256, s == 0, st) : march<T, 128, 8, false>(a, b, g, 256, s == 0, st);
+            else stream ? march<T, 64, 4, true>(a, b, g, 1024, s == 0, st) : march<T, 64, 4, false>(a, b, g, 1024, s == 0, st);
             cur ^= 1;
         }
         if (n > 0) {                                            // the ghost layers of the last state only
