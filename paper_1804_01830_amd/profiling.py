@@ -33,8 +33,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 DEVICE_SOURCES = ("csrc/passes.hip", "csrc/zfused.hpp", "csrc/z_serial_f32.hip", "csrc/z_serial_f64.hip",
                   "csrc/z_grouped_f32.hip", "csrc/z_grouped_f64.hip", "csrc/zreg.hpp", "csrc/z_reg_f32.hip",
-                  "csrc/lane_fft.hpp", "csrc/fft_device.hpp",
-                  "csrc/ddstress_internal.hpp")
+                  "csrc/plane.hpp", "csrc/plane_fwd_f32.hip", "csrc/plane_fwd_f64.hip", "csrc/plane_inv_f32.hip",
+                  "csrc/plane_inv_f64.hip", "csrc/lane_fft.hpp", "csrc/fft_device.hpp", "csrc/ddstress_internal.hpp")
 RELAX_SOURCES = ("csrc/relax.hip", "csrc/fft_device.hpp", "csrc/ddstress_internal.hpp")
 
 

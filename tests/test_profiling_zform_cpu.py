@@ -1,4 +1,5 @@
-"""The traffic summary takes the z launch that the library reported, whatever
+"""The sources behind a traffic summary are those of every kernel of the passes, and
+it takes the z launch that the library reported, whatever
 its kernel (synthetic counter files, no GPU)."""
 import csv
 import os
@@ -32,3 +33,11 @@ def test_traffic_of_the_register_form(tmp_path):
 def test_z_form_arguments_are_validated():
     out = B.ZLaunch()
     assert B.load().ddstress_plan_z_form(None, 1, out) == B.E_INVALID
+
+
+def test_the_digest_covers_the_sources_of_every_pass():
+    csrc = os.path.join(P.HERE, "csrc")
+    # host code, the plan build, and kernels outside the five passes
+    others = {"api.hip", "kernel_build.hip", "relax.hip", "stats.hip", "nye.hip"}
+    assert {f"csrc/{f}" for f in os.listdir(csrc) if f.endswith((".hip", ".hpp")) and f not in others} == \
+        set(P.DEVICE_SOURCES)
