@@ -78,6 +78,13 @@ __device__ __forceinline__ void round_here(cplx<T>& a) {
 
 // APART: the products with the eighth roots are rounded before they are added
 // (otherwise -ffp-contract joins the two).
+// Columns of length 64 (y), whose last stage is of radix 8, round them apart in every
+// kernel, separate and fused, so that all give the same bits: in the separate pass the
+// compiler sinks the last additions into the blocks of the conditional stores and does not
+// contract them there, which the others have to match, and which is said here rather
+// than left to it.
+template <int N>
+constexpr bool col_apart() { return N == 64; }
 template <bool FWD, bool APART = false, typename T>
 __device__ __forceinline__ void dft8(cplx<T>* v) {
     // even/odd split: two length-4 transforms joined with the eighth roots

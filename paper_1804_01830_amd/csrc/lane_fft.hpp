@@ -108,11 +108,6 @@ template <int N>
 constexpr int col_tw_count() {
     return N == 16 ? 4 * 2 : N == 32 ? 2 * 3 * 4 : N == 64 ? 2 * 7 * 4 : N == 128 ? 4 * 7 * 2 + 16 * 4 : 16 * 3 * 4;
 }
-// Whether a transform's last stage rounds its products apart: the compiler
-// sinks the last additions of the separate passes (k_col_fft) into the blocks of their
-// conditional stores, so a last stage of radix 8 (N = 64) is not contracted there.
-template <int N>
-constexpr bool col_apart() { return N == 64; }
 // Index (in 1 / N turns) of entry e of the twiddle table.
 template <int N>
 __device__ __forceinline__ int col_tw_index(int e) {

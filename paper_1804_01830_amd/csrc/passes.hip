@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(512) k_col_fft(const cplx<T>* in, cplx<T>* out
         const int i = j + Tc * m;
         reg[m] = (valid && i < g.n_in) ? src[i * irs] : cplx<T>{T(0), T(0)};
     }
-    fft_regs<T, N, E, FWD>(reg, lds, ColMajor{tk}, c, j, tw + (N - 1));
+    fft_regs<T, N, E, FWD, false, false, col_apart<N>()>(reg, lds, ColMajor{tk}, c, j, tw + (N - 1));
     if (!valid) return;
     cplx<T>* dst = out + plane * g.ops + outer * g.oos + col;
 #pragma unroll
