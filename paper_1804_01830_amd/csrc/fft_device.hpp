@@ -221,14 +221,15 @@ __device__ __forceinline__ void buf_store_cplx<float>(__amdgpu_buffer_rsrc_t r, 
 // offset in a scalar register the compiler lets the next instruction overwrite
 // them, which gave wrong values (the last lanes of each row of 16 stored the
 // overwriting value when the store had to wait). With the whole offset in the
-// vector register it keeps its distance.
+// vector register it keeps its distance. (The sum of a dropped store, a resource's size
+// plus a row, may pass 2^31; it stays below 2^32.)
 template <>
 __device__ __forceinline__ void buf_store_cplx<double>(__amdgpu_buffer_rsrc_t r, int voff, int soff, cplx<double> v) {
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
     const unsigned long long a = (unsigned long long)__double_as_longlong(v.x);
     const unsigned long long b = (unsigned long long)__double_as_longlong(v.y);
     const u4 d = {(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
-    __builtin_amdgcn_raw_buffer_store_b128(d, r, voff + soff, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(d, r, (int)((uint32_t)voff + (uint32_t)soff), 0, 0);
 }
 
 __device__ __forceinline__ void buf_store_real(__amdgpu_buffer_rsrc_t r, int voff, int soff, float v) {
