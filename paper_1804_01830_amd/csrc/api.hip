@@ -463,14 +463,15 @@ ZGeom z_geom(const Shape& s, int tk, int stk, int nb, bool kin, bool kout) {
 // us, whole FP32 calls of eight realisations on the spectrum of a plan of one,
 // this tile / the spectrum's own (a plan of eight): three channels 128x128x32 437 / 478 (418),
 // 256x256x32 2046 / 2372 (1999), 128x128x64 865 / 1133 (847); six 592 / 774 (568), 2871 / 3557 (2789), 1232 /
-// 1527 (1198); nine 811 / 1067 (785), 3926 / 4962 (3846).
+// 1527 (1198); nine 811 / 1067 (785), 3926 / 4962 (3846). The wider tile of the single-group form does
+// not pay within 64 MB: three of 20x20x20 31.3 / 29.9, of 20x20x40 41.7 / 38.3, but of 30x40x50 56 / 64.
 int z_call_tile(const ddstress_plan_s* p, int nb) {
     const Shape& s = p->shape;
     if (nb <= p->tuned_batch || s.zg != 1) return s.tkz;
     for (int tk = default_z_tk(s.P[2], s.C, 1, nb, s.elem, s.N[2], call_bytes(s, nb)); tk > s.tkz; tk /= 2) {
         ZGeom g = z_geom(s, tk, s.tkz, nb, false, false);
         z_launch_plan(s.P[2], p->ez, 1, g, tk, s.elem);
-        if (z_retile_ok(s.P[2], g, tk, s.elem)) return tk;
+        if (z_retile_ok(s.P[2], g, tk, s.elem) && (g.form == kZReg || call_bytes(s, nb) > kLastCache / 4)) return tk;
     }
     return s.tkz;
 }
