@@ -164,7 +164,9 @@ typedef struct {
     int32_t tk_y;          /* consecutive kx columns per block of the y passes */
     int32_t tk_z;          /* consecutive kx columns per block of the fused z pass */
     int32_t ex, ey, ez;    /* element classes of the x, y and fused z passes (0: default) */
-    int32_t z_groups;      /* fused z thread groups: 1 or C (0: default, C when batch >= 16) */
+    int32_t z_groups;      /* fused z thread groups: 1 or C (0: default: C when batch >= 16, but 1 for the lengths
+                              that the register form (FP32: Pz 16 with C > 3, 32, 64, and 128 with C < 9) or
+                              the wave form (FP64: Pz 8 to 128 with C = 3, 32 to 128 with C = 6) takes) */
     int32_t yx;            /* inverse y and x: 1 two passes, 2 one fused kernel that keeps each
                               (realisation, component, z) plane in LDS (by name for FP32 with Py = 256,
                               Px = 256 and an open y axis only), 0 default (fused wherever a plane

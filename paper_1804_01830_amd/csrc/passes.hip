@@ -480,7 +480,8 @@ static int col_tw(int Py) { return Py == 16 ? 8 : Py == 32 ? 24 : Py == 64 ? 56 
 // in us: FP32 32x32x4 9.1 / 13.6, 64^3 22 / 31, 100x75x20 (256, M = 128) 34 /
 // 45 (the fused kernels before these), 30x100x20 (256, M = 32) 26 / 19 (not
 // taken); FP64 33x20x9 12 / 15, 64^3 38 / 48. Closest: periodic 64x128 rows,
-// two realisations, 22.4 / 23.0 (FP64 30.2 / 30.9).
+// two realisations, 22.4 / 23.0 (FP64 30.2 / 30.9). How many planes a launch needs:
+// plane_min.
 bool plane_fits(int Py, int M, int ny, int elem_bytes) {
     const bool lengths = M >= 8 && M <= 128 && Py >= 16 && (Py <= 128 || (Py == 256 && M == 128 && elem_bytes == 4));
     if (!lengths || ny < 1 || ny > Py) return false;

@@ -494,10 +494,12 @@ struct ddstress_relax_s {
     void iterate(int n, hipStream_t st) {
         const RelaxGeom<T> g = make_geom<T>(desc, dt, A, B);
         // Tiles of 64 x 4 columns, or of 128 x 8 on large films that they fill exactly:
-        // those have less halo, but few blocks, so a ragged film leaves CUs idle. In us per step,
-        // 128 x 8 / 64 x 4: 256x256x64 28.7 / 30.5, 128x128x32 7.9 / 8.6, 200x180x40 22.1 / 15.9,
-        // 70x33x12 FP64 8.5 / 5.8. The force streams past the caches once a step touches more than
-        // the 256 MB that the last one holds: 256x256x64 FP64 68.3 against 72.9, FP32 (154 MB) 35.5 against 29.4.
+        // those have less halo, but few blocks, so a ragged film leaves CUs idle. us per step (of
+        // twenty in a call), 128 x 8 / 64 x 4: 256x256x64 FP32 26.2 / 27.2, FP64 54.8 / 57.5, 128x128x32 FP32 7.1 / 7.7 (FP64
+        // 11.9 / 11.7), 200x180x40 21.9 / 13.8, 300x300x100 104 / 81, 70x33x12 FP64 8.2 / 5.6; but 250x250x60 FP64 53 / 62.
+        // The force streams past the caches once a step touches more than the 256 MB that the last one holds,
+        // streamed / not: 256x256x64 FP64 (302 MB) 54.7 / 59.8, 256x256x128 FP32 55.9 / 65.3; within it FP32 256x256x64
+        // (151 MB) 31.1 / 26.2. (64 x 4 tiles are nearly indifferent: 300x300x100 FP64 173 / 167.)
         const bool large = desc.n[0] % 128 == 0 && desc.n[1] % 8 == 0 && nodes() >= (int64_t(1) << 19);
         const bool stream = (size_t)9 * nodes() * sizeof(T) > ((size_t)256 << 20);
         for (int s = 0; s < n; ++s) {

@@ -60,9 +60,10 @@ __device__ __forceinline__ int spec_col(const ZGeom& g, int part, int c) {
 // strip (g.nyq groups, see z_nyq_groups) the last tile is the strip, whose
 // blocks hold the column kx = M at ky = q tk + c for group q. A strip lane
 // reads and writes its own row (one cache line per value, against one per
-// tk values elsewhere), so each strip block takes one realisation: blocks
-// q B + b come first, short, and never form the launch's tail. The following
-// blocks take the other kx tiles by z_block_coords and every realisation.
+// tk values elsewhere), so each strip block takes few realisations (g.sb: one for
+// each of its waves in the wave and register forms, otherwise one): the blocks of
+// all groups and realisations come first, short, and never form the launch's tail. The
+// following blocks take the other kx tiles by z_block_coords and every realisation.
 //
 // Logical block of this workgroup: the strip's blocks are the first
 // workgroups, which the hardware deals to the eight XCDs in turn (so each
